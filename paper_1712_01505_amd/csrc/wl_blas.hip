@@ -11,6 +11,8 @@
 // rho, convergence) run on the device so the host only polls occasionally.
 //
 // Inner product <a, b> = sum conj(a_i) b_i; norms and dots accumulate in FP64.
+#include <algorithm>
+
 #include "wl_internal.h"
 
 namespace wl {
@@ -325,12 +327,9 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
     }
     }
     if constexpr (NV > 0) {
-        block_sum<NV>(red, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int k = 0; k < NV; ++k)
-                p.partials[((size_t)k * gridDim.y + col) * p.nblk + blockIdx.x] = red[k];
-        }
+        const double sum = block_sum<NV>(red, lds);
+        if ((int)threadIdx.x < NV)
+            p.partials[((size_t)threadIdx.x * gridDim.y + col) * p.nblk + blockIdx.x] = sum;
     }
 }
 
@@ -423,15 +422,21 @@ hipError_t launch_accum(int pin, uint32_t V, int nrhs, void *x64, const void *e,
 // ---------------------------------------------------------------- finalize
 // One workgroup sums every (value, right-hand side) row of the partial
 // arrays in a fixed order and then runs the scalar recurrence per column.
-// Rows are summed G at a time; a pass loads U values of each of the G rows
-// per thread before it adds any of them.
-constexpr int FIN_THREADS = 1024;
+// A row of n partials is cut into S = min(16, ceil(n / 512)) slices, slice j
+// holding the blocks j, j + S, ... of 512 partials; one wavefront sums a
+// slice (8 loads per lane in flight), and a row's slices are then added in
+// order, so a row's sum depends on n alone.  All rows and slices of a batch
+// (at most FIN_TASKS of them) run side by side: a single workgroup is bound
+// by the latency of its dependent steps.  (Four rows at a time with all 16
+// wavefronts, their block sum ending in one thread, took 11.1, 4.2 and 3.6 us
+// for the three reductions of a BiCGStab iteration on 8^3 x 16 sites (8, 2
+// and 1 rows of 32 partials), now 3.3 us on average; 16 us for the 8 rows of
+// 2048 and 512 partials of a domain-wall CG on 16^3 x 32 x 8, now 6.3 us.)
+constexpr int FIN_WAVES = 16;    // wavefronts at most (one per slice of a batch)
+constexpr int FIN_TASKS = 256;   // slices per batch
+constexpr int FIN_BLOCK = 512;   // partials a wavefront loads at once
 constexpr int FIN_MAX = RED_NVAL_MAX * 64;  // values x right-hand sides per partial set
-// rows summed per pass: a template parameter G, 1 or 2 when the call has
-// that few rows, else 4 (measured: one pass of 8 rows took 13.8 us where
-// two passes of 4 took 12.1 us; a 1-row call with G = 1 5.8 us, with G = 4
-// 7.5 us)
-constexpr int FIN_U = 4;         // loads per thread per row and pass
+__host__ __device__ inline int fin_slices(int n) { return n > 16 * FIN_BLOCK ? 16 : n > 0 ? (n + FIN_BLOCK - 1) / FIN_BLOCK : 1; }
 
 __device__ __forceinline__ bool finite2(double a) { return isfinite(a); }
 __device__ __forceinline__ double2 cmul(double2 a, double2 b)
@@ -461,65 +466,54 @@ __device__ __forceinline__ RowRef fin_row(const FinParams &p, int c)
     return RowRef{p.C + (size_t)c * p.nblkC, p.lenC ? p.lenC[c % p.nrhs] : p.nblkC};
 }
 
-template <int FIN_G>
-__global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(FinParams p, int op)
+__global__ __launch_bounds__(64 * FIN_WAVES) void finalize_kernel(FinParams p, int op)
 {
-    __shared__ double lds[FIN_G * FIN_THREADS / 64];
+    __shared__ double part[FIN_TASKS];
     __shared__ double sums[3 * FIN_MAX];
     __shared__ double gsums[3 * FIN_MAX];
     const int nr = p.nrhs;
     const int na = p.nvalA * nr, nb = p.nvalB * nr, ncomb = na + nb + p.nvalC * nr;
-    for (int c0 = 0; c0 < ncomb; c0 += FIN_G) {
-        // one pass issues the loads of all G rows before any add: a single
-        // workgroup is bound by its load issue rate, not by latency
-        RowRef row[FIN_G];
-        int nmax = 0;
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+    // task slots per row: the slices of the longest set; the slots past a
+    // shorter row's own slices add zeros
+    const int smax = max(max(fin_slices(na ? p.nblkA : 0), fin_slices(nb ? p.nblkB : 0)), fin_slices(p.nvalC ? p.nblkC : 0));
+    const int rows = FIN_TASKS / smax;  // rows per batch
+    for (int c0 = 0; c0 < ncomb; c0 += rows) {
+        const int nrow = min(rows, ncomb - c0);
+        for (int task = wave; task < nrow * smax; task += nw) {
+            const RowRef row = fin_row(p, c0 + task / smax);
+            const int j = task % smax, ns = fin_slices(row.n);
+            double v = 0.0;
+            for (int base = j * FIN_BLOCK; j < ns && base < row.n; base += ns * FIN_BLOCK) {
+                double x[8];
 #pragma unroll
-        for (int g = 0; g < FIN_G; ++g) {
-            row[g] = c0 + g < ncomb ? fin_row(p, c0 + g) : RowRef{nullptr, 0};
-            nmax = max(nmax, row[g].n);
-        }
-        double v[FIN_G];
-#pragma unroll
-        for (int g = 0; g < FIN_G; ++g)
-            v[g] = 0.0;
-        for (int base = 0; base < nmax; base += FIN_U * FIN_THREADS) {
-            double x[FIN_G][FIN_U];
-#pragma unroll
-            for (int g = 0; g < FIN_G; ++g) {
-                if (base < row[g].n) {  // uniform: rows shorter than nmax stop early
-#pragma unroll
-                    for (int j = 0; j < FIN_U; ++j) {
-                        const int i = base + j * FIN_THREADS + (int)threadIdx.x;
-                        x[g][j] = row[g].p[i < row[g].n ? i : 0];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < FIN_U; ++j)
-                        x[g][j] = 0.0;
+                for (int k = 0; k < 8; ++k) {
+                    const int i = base + 64 * k + lane;
+                    x[k] = row.p[i < row.n ? i : base];
                 }
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (base + 64 * k + lane >= row.n)
+                        x[k] = 0.0;
+                // fixed pairwise order within a block of partials
+#pragma unroll
+                for (int w = 4; w > 0; w >>= 1)
+#pragma unroll
+                    for (int k = 0; k < w; ++k)
+                        x[k] += x[k + w];
+                v += x[0];
             }
-#pragma unroll
-            for (int g = 0; g < FIN_G; ++g) {
-#pragma unroll
-                for (int j = 0; j < FIN_U; ++j)
-                    if (base + j * FIN_THREADS + (int)threadIdx.x >= row[g].n)
-                        x[g][j] = 0.0;
-                // fixed pairwise order within a pass
-#pragma unroll
-                for (int w = FIN_U / 2; w > 0; w >>= 1)
-#pragma unroll
-                    for (int j = 0; j < w; ++j)
-                        x[g][j] += x[g][j + w];
-                v[g] += x[g][0];
-            }
+            v = wave_sum(v);
+            if (lane == 0)
+                part[task] = v;
         }
-        block_sum<FIN_G>(v, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int g = 0; g < FIN_G; ++g)
-                if (c0 + g < ncomb)
-                    sums[c0 + g] = v[g];
+        __syncthreads();
+        if ((int)threadIdx.x < nrow) {
+            double a = part[threadIdx.x * smax];
+#pragma unroll 4
+            for (int j = 1; j < smax; ++j)
+                a += part[threadIdx.x * smax + j];
+            sums[c0 + threadIdx.x] = a;
         }
         __syncthreads();
     }
@@ -865,13 +859,13 @@ hipError_t launch_finalize(int op, const FinParams &p, hipStream_t st)
 {
     if (p.nrhs > 64 || p.nvalA * p.nrhs > FIN_MAX || p.nvalB * p.nrhs > FIN_MAX || p.nvalC * p.nrhs > FIN_MAX)
         return hipErrorInvalidValue;
+    // one wavefront per slice, up to 16; at least one thread per row of a
+    // batch and per column
     const int rows = (p.nvalA + p.nvalB + p.nvalC) * p.nrhs;
-    if (rows <= 1)
-        hipLaunchKernelGGL(finalize_kernel<1>, dim3(1), dim3(FIN_THREADS), 0, st, p, op);
-    else if (rows <= 2)
-        hipLaunchKernelGGL(finalize_kernel<2>, dim3(1), dim3(FIN_THREADS), 0, st, p, op);
-    else
-        hipLaunchKernelGGL(finalize_kernel<4>, dim3(1), dim3(FIN_THREADS), 0, st, p, op);
+    const int tasks = rows * std::max(std::max(fin_slices(p.nvalA ? p.nblkA : 0), fin_slices(p.nvalB ? p.nblkB : 0)),
+                                      fin_slices(p.nvalC ? p.nblkC : 0));
+    const int nw = std::max(1, std::min(FIN_WAVES, tasks));
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64 * nw), 0, st, p, op);
     return hipGetLastError();
 }
 

@@ -383,34 +383,30 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
     }
     if constexpr (NV > 0) {
         if constexpr (!MULTI) {
-            block_sum<NV>(red, lds_red);
-            if (threadIdx.x == 0) {
-#pragma unroll
-                for (int k = 0; k < NV; ++k)
-                    p.partials[((size_t)k * p.nrhs + rhs) * p.nblk + bt] = red[k];
-            }
+            const double sum = block_sum<NV>(red, lds_red);
+            if ((int)threadIdx.x < NV)
+                p.partials[((size_t)threadIdx.x * p.nrhs + rhs) * p.nblk + bt] = sum;
         } else {
-            // per right-hand side: wavefront sums, then thread r adds the
-            // wavefronts of copy r in order
+            // per right-hand side: wavefront sums, then thread NV r + k adds
+            // those of value k over the wavefronts of copy r in order
             const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6, nwv = (int)blockDim.x >> 6;
+            double ws[(NV + 3) / 4];
+            wave_sums<NV>(red, ws);
+            if ((lane & 15) == 0) {
 #pragma unroll
-            for (int i = 0; i < NV; ++i)
-                red[i] = wave_sum(red[i]);
-            if (lane == 0) {
-#pragma unroll
-                for (int i = 0; i < NV; ++i)
-                    lds_red[i * nwv + wv] = red[i];
+                for (int q = 0; q < (NV + 3) / 4; ++q) {
+                    const int i = wave_value<NV>(q, lane >> 4);
+                    if (i >= 0)
+                        lds_red[i * nwv + wv] = ws[q];
+                }
             }
             __syncthreads();
-            if ((int)threadIdx.x < g.RW) {
-                const int per = g.NB >> 6, r = (int)threadIdx.x;
-#pragma unroll
-                for (int k = 0; k < NV; ++k) {
-                    double a = 0.0;
-                    for (int j = 0; j < per; ++j)
-                        a += lds_red[k * nwv + r * per + j];
-                    p.partials[((size_t)k * p.nrhs + grp * g.RW + r) * p.nblk + bt] = a;
-                }
+            if ((int)threadIdx.x < NV * g.RW) {
+                const int per = g.NB >> 6, r = (int)threadIdx.x / NV, k = (int)threadIdx.x % NV;
+                double a = 0.0;
+                for (int j = 0; j < per; ++j)
+                    a += lds_red[k * nwv + r * per + j];
+                p.partials[((size_t)k * p.nrhs + grp * g.RW + r) * p.nblk + bt] = a;
             }
         }
     }

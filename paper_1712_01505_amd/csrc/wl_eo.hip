@@ -216,12 +216,9 @@ __global__ __launch_bounds__(256) void eo_hop_kernel(EoParams p)
         }
     }
     if constexpr (NV > 0) {
-        block_sum<NV>(red, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int k = 0; k < NV; ++k)
-                p.partials[((size_t)k * p.nrhs + rhs) * p.nblk + blockIdx.x] = red[k];
-        }
+        const double sum = block_sum<NV>(red, lds);
+        if ((int)threadIdx.x < NV)
+            p.partials[((size_t)threadIdx.x * p.nrhs + rhs) * p.nblk + blockIdx.x] = sum;
     }
 }
 

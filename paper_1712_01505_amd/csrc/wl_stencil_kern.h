@@ -215,20 +215,10 @@ __global__ __launch_bounds__(256) void twalk_kernel(StencilParams p, int T, uint
         }
     }
     if constexpr (NV > 0) {
-        if (lg == 0) {
-            block_sum<NV>(red, lds);
-            if (threadIdx.x == 0) {
-#pragma unroll
-                for (int k = 0; k < NV; ++k)
-                    p.partials[((size_t)k * p.nrhs + rhs) * p.nblk + bt] = red[k];
-            }
-        } else {
-            block_sum_lanes<NV>(red, lds, lg);
-            if ((int)threadIdx.x < (1 << lg)) {
-#pragma unroll
-                for (int k = 0; k < NV; ++k)
-                    p.partials[((size_t)k * p.nrhs + (grp << lg) + threadIdx.x) * p.nblk + bt] = red[k];
-            }
+        const double sum = block_sum_lanes<NV>(red, lds, lg);
+        if ((int)threadIdx.x < (NV << lg)) {
+            const int k = (int)threadIdx.x >> lg, j = (int)threadIdx.x & ((1 << lg) - 1);
+            p.partials[((size_t)k * p.nrhs + (grp << lg) + j) * p.nblk + bt] = sum;
         }
     }
 }
@@ -350,20 +340,16 @@ __global__ __launch_bounds__(512) void stencil_kernel(StencilParams p)
     }
     if constexpr (NV > 0) {
         if constexpr (R == 1) {
-            block_sum_lanes<NV>(red, lds, lg);
-            if ((int)threadIdx.x < (1 << lg)) {
-#pragma unroll
-                for (int k = 0; k < NV; ++k)
-                    p.partials[((size_t)k * p.nrhs + (grp << lg) + threadIdx.x) * p.nblk + bt] = red[k];
+            const double sum = block_sum_lanes<NV>(red, lds, lg);
+            if ((int)threadIdx.x < (NV << lg)) {
+                const int k = (int)threadIdx.x >> lg, j = (int)threadIdx.x & ((1 << lg) - 1);
+                p.partials[((size_t)k * p.nrhs + (grp << lg) + j) * p.nblk + bt] = sum;
             }
         } else {
-            block_sum<NV * R>(red, lds);
-            if (threadIdx.x == 0) {
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int k = 0; k < NV; ++k)
-                        p.partials[((size_t)k * p.nrhs + r0 + r) * p.nblk + bt] = red[NV * r + k];
+            const double sum = block_sum<NV * R>(red, lds);
+            if ((int)threadIdx.x < NV * R) {
+                const int r = (int)threadIdx.x / NV, k = (int)threadIdx.x % NV;
+                p.partials[((size_t)k * p.nrhs + r0 + r) * p.nblk + bt] = sum;
             }
         }
     }
@@ -605,12 +591,9 @@ __device__ __forceinline__ void multi_item(const MultiEntry *E, int n, uint32_t 
     }
     if (red != RED_NONE) {  // uniform: every thread of the workgroup takes part
         __shared__ double lds_mr[RED_NVAL_MAX * 8];
-        block_sum<RED_NVAL_MAX>(rv, lds_mr);
-        if (threadIdx.x == 0) {
-            const int nv = red_nval(red);
-            for (int k = 0; k < nv; ++k)
-                p.partials[((size_t)k * p.pncol + p.pcol0 + r0) * p.pstride + lt] = rv[k];
-        }
+        const double sum = block_sum<RED_NVAL_MAX>(rv, lds_mr);
+        if ((int)threadIdx.x < red_nval(red))
+            p.partials[((size_t)threadIdx.x * p.pncol + p.pcol0 + r0) * p.pstride + lt] = sum;
     }
 }
 
