@@ -128,14 +128,20 @@ struct EoParams {
     int parity;          // of the output sites
     int nrhs;
     double c_self, c_hop;  // out = c_self self + c_hop H in
-    uint32_t V, Vh;      // set by the launcher
+    const void *res;     // FP64 / FP32: out = res - (c_self self + c_hop H in); else null
+    uint32_t V, Vh;      // this and the rest: set by the launcher
     FastDiv fxh, fy, fz;
-    int nblk;
+    int nblk;            // site tiles per right-hand side (padded to a multiple of 8 for several)
+    uint32_t ng;         // right-hand sides
+    FastDiv f_ng;
+    int xcd;             // tile order: 1 one contiguous range per XCD, >= 2 slabs (half lattice)
+    SlabOrder slab;
+    float one;           // 1.0 (see project())
 };
 hipError_t launch_eo_hop(int prec, int dagger, int red, EoParams p, hipStream_t st);
 hipError_t launch_eo_copy(int prec, bool split, const int *L, int nrhs, const void *full_in, void *full_out,
                           void *even, void *odd, hipStream_t st);
-int eo_partials(uint32_t Vh);  // per-right-hand-side partials of one eo_hop launch
+int eo_partials(uint32_t Vh, int nrhs);  // per-right-hand-side partials of one eo_hop launch
 EoParams eo_params(const wl_op *op, int parity, int nrhs);  // links, extents, parity
 
 // ---- stencil (wl_stencil.hip)

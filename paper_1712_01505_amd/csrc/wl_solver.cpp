@@ -409,7 +409,7 @@ struct Engine {
     {
         if (!lats.empty())
             return stencil_multi(out, in, dagger ^ adj, red, aux, slot, loop, aux2, aux3);
-        if (eo) {  // out = (1 - kappa^2 H_eo H_oe) in on even half fields
+        if (eo) {  // out = (1 - kappa^2 H_eo H_oe) in on even half fields (apply 3: aux - that)
             EoParams a = eo_params(op, 1, nrhs);
             a.in = in;
             a.out = eo_tmp;
@@ -419,7 +419,10 @@ struct Engine {
             EoParams b = eo_params(op, 0, nrhs);
             b.in = eo_tmp;
             b.self = in;
-            b.dotv = aux;
+            if (apply == 3)
+                b.res = aux;
+            else
+                b.dotv = aux;
             b.dotv2 = aux2;
             b.dotv3 = aux3;
             b.out = out;
@@ -428,7 +431,7 @@ struct Engine {
             b.skip = loop ? sc : nullptr;
             b.partials = slot >= 0 ? part[slot] : nullptr;
             if (slot >= 0) {
-                nblk[slot] = eo_partials(V);
+                nblk[slot] = eo_partials(V, nrhs);
                 nval[slot] = stencil_nval(red);
             }
             ++stencil_calls;
@@ -769,7 +772,7 @@ struct Engine {
     {
         int rc;
         void *w = v[1], *r = v[0];
-        if (lats.empty() && !eo && op->ns == 0 && (prec == WL_F64 || prec == WL_F32)) {
+        if (lats.empty() && op->ns == 0 && (prec == WL_F64 || prec == WL_F32)) {
             // one pass: r = b - D x with |r|^2 in the stencil's epilogue
             if ((rc = stencil(r, x, 0, RED_NORM, b, 0, false, nullptr, nullptr, 3)))
                 return rc;
