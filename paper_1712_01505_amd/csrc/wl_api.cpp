@@ -262,33 +262,168 @@ static void save_tune_cache_locked()
     f << "]}\n";
 }
 
-// Untuned defaults (measured on MI355X at 32^3 x 64): one right-hand side
-// runs the pipelined hop loop with small workgroups; several right-hand
-// sides share each link load across RHS_per_thread spinors.
-static LaunchCfg default_launch(const wl_op *op, int nrhs)
+static bool launch_ok(const wl_op *op, int nrhs, const LaunchCfg &c);
+
+// Brick walk for an untuned launch: of the shapes that tile the lattice, the
+// one with the least estimated time.  A CU holds k workgroups (by their LDS
+// stage and by the wavefronts their registers allow: one per SIMD in FP64,
+// two in FP32, two with a fused reduction and three without in 16 bits); the
+// chip walks its units in rounds of 256 k workgroups, each of T + 1 slices
+// (the walk's start costs about one), and a slice costs its sites' own bytes
+// plus its halo's, which come from L2 (half weight; the x faces are single
+// sites of other rows, six times that).  The fastest measured shape at 32^3 x 64
+// is the estimate's in FP64 and FP32 (32 x 2 x 4, walks of 32 and 16) and
+// within 1 % of it for the 16-bit apply; with a reduction 16 bits run best in
+// bricks of one wavefront (FP16, the eight BiCGStab values: 126 us, 256
+// sites 137), whose barriers wait for nobody.  False if no shape fits.
+static bool brick_default(const wl_op *op, int nrhs, int red, LaunchCfg &best)
+{
+    const int *L = op->g.dims, prec = op->prec;
+    const double site = 2.0 * spinor_site_bytes(prec) + 4.0 * link_site_bytes(prec), sp = spinor_site_bytes(prec);
+    const bool half = prec >= WL_BF16S;
+    const int nb_lo = half && red != RED_NONE ? 64 : 128, nb_hi = half && red != RED_NONE ? 64 : 256;
+    const int waves_cu = prec == WL_F64 ? 4 : half && red == RED_NONE ? 12 : 8;
+    double least = INFINITY;
+    for (int bx = 32; bx >= 4; --bx) {
+        if (L[0] % bx != 0)
+            continue;
+        for (int by = 1; by <= L[1] && bx * by <= nb_hi; ++by) {
+            if (L[1] % by != 0)
+                continue;
+            for (int bz = 1; bz <= L[2] && bx * by * bz <= nb_hi; ++bz) {
+                const int nb = bx * by * bz;
+                if (L[2] % bz != 0 || nb % 64 != 0 || nb < nb_lo || !brick_ok(L, prec, bx, by, bz, 1, 0, 1))
+                    continue;
+                const int fx = bx == L[0] ? 0 : 2 * nb / bx, fy = by == L[1] ? 0 : 2 * nb / by,
+                          fz = bz == L[2] ? 0 : 2 * nb / bz;
+                const int nsp = nb + (fx + fy + fz + 63) / 64 * 64;
+                int k = (int)((LDS_PER_CU - 1024) / ((size_t)nsp * spinor_site_bytes(prec)));
+                k = std::min(k, std::max(1, waves_cu / (nb / 64)));
+                const double idle = prec == WL_F64 && nb == 192 ? 1.15 : 1.0;  // a SIMD without a wavefront
+                const double slice = (nb * site + 0.5 * sp * (6.0 * fx + fy + fz)) * idle;
+                const double units = (double)(L[0] / bx) * (L[1] / by) * (L[2] / bz) * nrhs;
+                for (int T = 2; T <= 32 && T <= L[3]; ++T) {
+                    if (L[3] % T != 0)
+                        continue;
+                    const double cost = std::ceil(units * (L[3] / T) / (256.0 * k)) * k * (T + 1) * slice;
+                    LaunchCfg c{nb, 1, 1, VAR_BRICK, 1};
+                    c.bx = bx;
+                    c.by = by;
+                    c.bz = bz;
+                    c.tsteps = T;
+                    if (cost < least && launch_ok(op, nrhs, c)) {
+                        least = cost;
+                        best = c;
+                    }
+                }
+            }
+        }
+    }
+    return std::isfinite(least);
+}
+
+// Walk length (variant 4, 5 or 6: columns of 4, 8, 16 sites) of an untuned
+// FP64 t-walk, whose registers leave one wavefront per SIMD: the most
+// wavefronts that still run in one round of the chip's 1024 SIMDs (16^3 x 64:
+// 39.6 us with 4, 38.1 with 8; 20^3 x 40: 62.2 and 48.5 us; 16^3 x 32: 23 and
+// 32 us); where every length needs several rounds, 8 if it divides, else 4
+// (24^3 x 48, four columns: 437 us with 8).  0 if none divides Lt.
+static int twalk_default(const int *L, int cols)
+{
+    const long w = ((long)L[0] * L[1] * L[2] + 63) / 64 * cols;
+    for (int v = 4; v <= 6; ++v)
+        if (L[3] % (4 << (v - 4)) == 0 && w * (L[3] / (4 << (v - 4))) <= 1024)
+            return v;
+    return L[3] % 4 != 0 ? 0 : cols > 1 && L[3] % 8 == 0 ? 5 : 4;
+}
+
+// Launch shape where neither the caller nor the tuner has chosen one (times
+// on MI355X, us per launch).
+//
+// Tile order: z-slabs per XCD from about 400 000 sites (all columns), whose
+// t-slices the L2s would otherwise lose (32 x 16 x 24 x 40, FP32: 36 against
+// 41), else one contiguous range per XCD (16^3 x 64: 20 against 25); plain
+// order leaves each XCD's L2 with an eighth of every neighbourhood (20^3 x 40,
+// FP32: 39.3 plain, 26.3 contiguous).
+static LaunchCfg default_launch(const wl_op *op, int nrhs, int red)
 {
     const int prec = op->prec;
+    const int *L = op->g.dims;
+    const uint64_t V = op->V, VN = V * (uint64_t)nrhs;
     LaunchCfg c;
-    if (nrhs == 1) {
-        c.rpt = 1;
-        if (prec == WL_F64 || prec == WL_F32) {
-            c.block = 256;
-            c.xcd = slab_ok(op->g.dims, 256, 2) ? 2 : 0;
-            c.var = prec == WL_F64 ? 1 : 2;
-        } else {
-            c.block = 128;
-            c.xcd = 1;
-            c.var = 2;
-        }
+    c.rpt = 1;
+    const auto order = [&](int tile) { return VN >= 400000 && slab_ok(L, tile, 2) ? 2 : 1; };
+    if (nrhs > 1 && VN < (1u << 18)) {
+        // several columns of a small lattice: four across the lanes, one link
+        // fetch per instruction for all of them, and fewest instructions in
+        // flight (8^3 x 16 x 8 domain wall, FP64: 9.4, as a t-walk 17.6)
+        c.lanes = nrhs % 4 == 0 ? 4 : nrhs % 2 == 0 ? 2 : 1;
+        c.var = prec == WL_F64 ? 1 : 2;
         return c;
     }
-    // several right-hand sides: interleave them across the lanes of each
-    // wavefront (one link fetch per instruction serves all of them)
-    c.block = 256;
-    c.xcd = 1;
-    c.rpt = 1;
+    if (op->ns > 0) {
+        // domain wall: two slices across the lanes share a site's links (two
+        // beat four: 16^3 x 32 x 8 FP32 59.8 and 71.0; 32^3 x 64 x 8 1337 and
+        // 1717); FP64 as a t-walk (16^3 x 32 x 8: 107.5, pipelined 151.6)
+        c.lanes = nrhs % 2 == 0 ? 2 : 1;
+        c.block = 128;
+        const int tw = prec == WL_F64 ? twalk_default(L, nrhs) : 0;
+        c.var = tw ? tw : prec == WL_F64 ? 1 : 2;
+        c.xcd = tw ? 1 : order(c.block / c.lanes);
+        return c;
+    }
+    // 16-bit fields beyond the 256 MB Infinity Cache; within it the pipelined
+    // hops have their reuse from there (32^4: 40.7, brick walk 54; 32^3 x 64:
+    // 112 and 103 in BF16, 113 and 94 in FP16)
+    const bool big16 = prec >= WL_BF16S && VN * 104 + V * 96 > ((uint64_t)(nrhs > 1 ? 384 : 256) << 20);
+    if (nrhs == 1) {
+        // the brick walk reads every neighbour from LDS and pays off once its
+        // long walks fill the chip: 32^3 x 64 FP64 328 against 408 pipelined,
+        // FP32 162 against 191; 24^3 x 48 FP64 126 against 136; 32 x 16 x 24 x
+        // 64 FP32 with two sums 77 against 84.  BF16 with the eight BiCGStab
+        // values stays pipelined (147, in bricks 153)
+        const bool brick = prec == WL_F64   ? V >= (1u << 19)
+                           : prec == WL_F32 ? V >= (3u << 18)
+                                            : big16 && !(prec == WL_BF16S && (red == RED_BICG || red == RED_SR));
+        if (brick && brick_default(op, 1, red, c))
+            return c;
+        if (prec == WL_F64) {
+            // t-walk from about 2^16 sites (16^3 x 32: 23.0 against 26.1; 28 x 22 x
+            // 26 x 36: 130 against 138), below that one wavefront per workgroup
+            // (12^3 x 24: 8.4, with 256 threads 9.4; 8^3 x 16: 6.0 and 7.9)
+            const int tw = V >= (1u << 16) ? twalk_default(L, 1) : 0;
+            c.block = 64;
+            c.var = tw ? tw : 1;
+            return c;
+        }
+        // pipelined one hop ahead, or two: in FP32 from 2^17 sites (24^3 x 48
+        // 49.0, one 53.9; 16^3 x 32 11.6, one 11.3), in 16 bits on the smallest
+        // lattices, where only the chain of loads counts
+        c.var = (prec == WL_F32 ? V > (1u << 17) : V <= (1u << 14)) ? 2 : 1;
+        c.block = V < (1u << 16) ? 64 : 256;
+        c.xcd = order(c.block);
+        return c;
+    }
+    // several right-hand sides.  FP32: bricks, one column each (24^3 x 48, 12
+    // columns: 513, four across lanes 690; 16^3 x 32, four: 30.7 and 38).  FP64:
+    // bricks where they span 32 sites in x (32^4, two: 350 and 461 pipelined),
+    // else t-walks (24^3 x 48, four: 437, bricks 455, pipelined 484; 20^3 x 40,
+    // three: 148, pipelined 260).  16 bits: two columns across the lanes (16^3
+    // x 32, 12: 51.8, four 57.5), bricks beyond the cache (24^3 x 48, 12: 319,
+    // t-walk 338)
+    if ((prec == WL_F32 || (prec == WL_F64 && L[0] % 32 == 0) || (big16 && red == RED_NONE)) &&
+        brick_default(op, nrhs, red, c))
+        return c;
+    const int tw = prec == WL_F64 ? twalk_default(L, nrhs) : 0;
+    if (tw) {
+        c.block = VN < (1u << 20) ? 64 : 128;
+        c.var = tw;
+        return c;
+    }
+    c.lanes = prec >= WL_BF16S && nrhs % 2 == 0 ? 2 : 1;
+    c.block = c.lanes == 2 ? 128 : 256;
     c.var = prec == WL_F64 ? 1 : 2;
-    c.lanes = nrhs % 4 == 0 ? 4 : nrhs % 2 == 0 ? 2 : 1;
+    c.xcd = order(c.block / c.lanes);
     return c;
 }
 
@@ -372,7 +507,7 @@ LaunchCfg launch_for(const wl_op *op, int nrhs, int red, int dagger)
     }
     // first use of this (nrhs, reduction, dagger): search the op's choices
     // and the tune cache in the order above
-    LaunchCfg c = default_launch(op, nrhs);
+    LaunchCfg c = default_launch(op, nrhs, red);
     const int order[4][2] = {{red, dagger}, {red, 1 - dagger}, {RED_NONE, dagger}, {RED_NONE, 1 - dagger}};
     bool have = false;
     for (int k = 0; k < 4 && !have; ++k) {
@@ -1276,7 +1411,7 @@ int wl_autotune(const wl_op *op, int nrhs, int dagger, void *stream)
         }
         std::sort(timed.begin(), timed.end());
         float best_ms = INFINITY;
-        LaunchCfg best = default_launch(op, nrhs);
+        LaunchCfg best = default_launch(op, nrhs, red);
         for (size_t j = 0; j < timed.size() && j < 6 && e == hipSuccess; ++j) {
             const float ms = time_shape(cands[timed[j].second], red, 40);
             if (ms >= 0.f && ms < best_ms) {

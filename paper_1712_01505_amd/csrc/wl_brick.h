@@ -33,6 +33,9 @@
 // (16-bit storage: equal to rounding, as for the t-walk).
 #pragma once
 
+#include <atomic>
+#include <mutex>
+
 #include "wl_stencil_dev.h"
 
 namespace wl {
@@ -464,21 +467,45 @@ inline bool brick_setup(const int *L, int prec, int bx, int by, int bz, int T, B
     return true;
 }
 
+// Dynamic LDS granted to one kernel, per device; only ever raised.
+struct BrickLimit {
+    static constexpr int MAX_DEV = 64;
+    std::atomic<size_t> granted[MAX_DEV] = {};
+    std::mutex mu;
+    hipError_t raise(const void *fn, size_t smem)
+    {
+        int dev = 0;
+        const hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess)
+            return e;
+        if (dev < 0 || dev >= MAX_DEV)
+            return hipErrorInvalidDevice;
+        if (smem <= granted[dev].load(std::memory_order_acquire))
+            return hipSuccess;
+        std::lock_guard<std::mutex> lk(mu);
+        if (smem <= granted[dev].load(std::memory_order_relaxed))
+            return hipSuccess;
+        const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (r == hipSuccess)
+            granted[dev].store(smem, std::memory_order_release);
+        return r;
+    }
+};
+
 template <int P, int DAG, int RED, int APPLY, int MULTI>
 inline hipError_t brick_go1(dim3 grid, dim3 block, size_t smem, const StencilParams &p, const BrickGeom &g,
                             hipStream_t st)
 {
-    // dynamic LDS beyond the default 64 KB: raise this kernel's limit to what
-    // the launch needs (the kernel's static LDS counts against the same
-    // 160 KB, so the limit is set to the size asked for, not to the maximum)
-    static size_t granted = 65536;
-    if (smem > granted) {
-        const hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void *>(&brick_kernel<P, DAG, RED, APPLY, MULTI>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    // dynamic LDS beyond the default 64 KB: raise this kernel's limit on this
+    // device to what the launch needs (the kernel's static LDS counts against
+    // the same 160 KB, so the limit is set to the size asked for, not to the
+    // maximum), never lowering it under another thread's launch
+    if (smem > 65536) {
+        static BrickLimit limit;
+        const hipError_t e =
+            limit.raise(reinterpret_cast<const void *>(&brick_kernel<P, DAG, RED, APPLY, MULTI>), smem);
         if (e != hipSuccess)
             return e;
-        granted = smem;
     }
     hipLaunchKernelGGL((brick_kernel<P, DAG, RED, APPLY, MULTI>), grid, block, smem, st, p, g);
     return hipGetLastError();

@@ -1,0 +1,73 @@
+"""Launch shapes chosen without a tuner: valid for every geometry (on the
+CPU), and the same results as the straight-line kernel on the GPU."""
+import ctypes
+import random
+
+import numpy as np
+import pytest
+
+from paper_1712_01505_amd import inputs, wilson
+
+
+def _op(dims, prec, ns=0):
+    g = wilson.make_geom(dims)
+    if ns:
+        h = ctypes.c_void_p()
+        assert wilson.lib().wl_dw_op_create(ctypes.byref(g), -1.8, 0.05, ns, prec, 16, ctypes.byref(h)) == wilson.WL_OK
+        return h.value
+    return wilson.wl_op_create(g, 0.12, prec, 16)  # a dummy address: nothing is launched
+
+
+def test_default_shape_is_valid_everywhere():
+    rng = random.Random(1)
+    some = [2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 18, 20, 22, 24, 28, 31, 32, 40, 48, 64]
+    seen = set()
+    for k in range(1500):
+        dims = [rng.choice(some) for _ in range(4)] if k % 10 else [32, 32, 32, rng.choice([48, 64])]
+        prec, ns = rng.randrange(4), rng.choice([0, 0, 0, 1, 4, 6, 8])
+        nrhs = rng.choice([1, 1, 1, 2, 3, 4, 5, 8, 12, 16])
+        if max(ns, 1) * nrhs > 64:
+            continue
+        h = _op(dims, prec, ns)
+        c = wilson.wl_launch()
+        assert wilson.lib().wl_get_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK
+        assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK, (dims, prec, ns, nrhs, c.variant)
+        seen.add((prec, c.variant, ns > 0, nrhs > 1))
+        wilson.lib().wl_op_destroy(h)
+    for prec in (wilson.WL_F64, wilson.WL_F32, wilson.WL_F16S):
+        assert (prec, wilson.VAR_BRICK, False, False) in seen  # the sample reaches the bricks
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,nrhs", [((32, 32, 32, 20), 1), ((24, 12, 16, 12), 12), ((16, 16, 16, 20), 1),
+                                       ((20, 20, 12, 8), 3), ((18, 14, 10, 9), 5), ((32, 16, 16, 16), 2),
+                                       ((8, 8, 8, 16), 1), ((16, 16, 12, 40), 4), ((32, 32, 32, 25), 1)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "bf16", "f16"])
+def test_default_matches_straight_line(dims, nrhs, prec):
+    """FP64 / FP32: the same bits in every shape.  16 bits: the walks form a site in another
+    grouping, so results agree to the storage rounding (2^-8 BF16, 2^-11 FP16 of a site's
+    largest component, a few of them)."""
+    torch = pytest.importorskip("torch")
+    U = torch.from_numpy(inputs.near_unity_gauge((2, 2, 2, 2), 0.3, seed=3)).to("cuda")
+    Lx, Ly, Lz, Lt = dims
+    rep = [-(-n // 2) for n in (Lt, Lz, Ly, Lx)]
+    U = U.repeat(1, *rep, 1, 1)[:, :Lt, :Lz, :Ly, :Lx].contiguous()
+    g = torch.Generator(device="cuda").manual_seed(1)
+    psi = torch.view_as_complex(torch.randn(nrhs, Lt, Lz, Ly, Lx, 4, 3, 2, dtype=torch.float64, device="cuda",
+                                            generator=g))
+    op = wilson.Operator.create(U, 0.1255, wilson.PREC[prec])
+    src = op.pack(psi)
+    outs = []
+    for shape in (None, (64, 1, 0, 0, 1)):
+        if shape:
+            assert wilson.try_set_launch(op.handle, nrhs, *shape)
+        for dagger in (False, True):
+            out = op.new_field(nrhs)
+            op.apply_packed(out, src, nrhs, dagger)
+            outs.append(out)
+    for got, ref in ((outs[0], outs[2]), (outs[1], outs[3])):
+        if prec in ("f64", "f32"):
+            assert torch.equal(got, ref)
+        else:
+            a, b = op.unpack(got, nrhs), op.unpack(ref, nrhs)
+            assert float((a - b).norm() / b.norm()) < (2.0 ** -7 if prec == "bf16" else 2.0 ** -10)
