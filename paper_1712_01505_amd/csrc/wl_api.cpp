@@ -365,6 +365,16 @@ static LaunchCfg default_launch(const wl_op *op, int nrhs, int red)
         // domain wall: two slices across the lanes share a site's links (two
         // beat four: 16^3 x 32 x 8 FP32 59.8 and 71.0; 32^3 x 64 x 8 1337 and
         // 1717); FP64 as a t-walk (16^3 x 32 x 8: 107.5, pipelined 151.6)
+        // bricks that span 32 sites in x, one slice each, once three t-slices
+        // of all columns exceed the 32 MB of L2, from where the pipelined hops
+        // take their t neighbours (32^3 x 64 x 8: FP64 2697 and 3203, FP32 1179
+        // and 1371, FP16 811 and 846; 32^2 x 16 x 16 x 12, FP32: 240 and 304;
+        // below the line, 32 x 16 x 24 x 40 x 8, FP32: 321 and 300)
+        if (L[0] % 32 == 0 && 3.0 * spinor_site_bytes(prec) * L[0] * L[1] * L[2] * nrhs > 32.0 * (1 << 20) &&
+            brick_default(op, nrhs, RED_NONE, c)) {
+            c.xcd = 0;
+            return c;
+        }
         c.lanes = nrhs % 2 == 0 ? 2 : 1;
         c.block = 128;
         const int tw = prec == WL_F64 ? twalk_default(L, nrhs) : 0;
@@ -430,8 +440,8 @@ static LaunchCfg default_launch(const wl_op *op, int nrhs, int red)
 static bool launch_ok(const wl_op *op, int nrhs, const LaunchCfg &c)
 {
     const int prec = op->prec;
-    if (op->ns > 0 && (c.rpt != 1 || c.var == 3 || c.var > 6 || nrhs % op->ns != 0))
-        return false;  // domain wall: one slice per thread, variants 0..2 and the t-walks
+    if (op->ns > 0 && (c.rpt != 1 || c.var == 3 || (c.var == VAR_BRICK && c.lanes != 1) || nrhs % op->ns != 0))
+        return false;  // domain wall: one slice per thread, variants 0..2, the walks, one slice per brick
     // columns across lanes: at least 64 sites per workgroup, 32 for the
     // t-walks; the brick walk takes rhs_lanes right-hand sides per workgroup
     const bool lanes_ok = c.lanes == 1 || ((c.lanes == 2 || c.lanes == 4 || c.lanes == 8) && c.rpt == 1 &&
@@ -443,7 +453,7 @@ static bool launch_ok(const wl_op *op, int nrhs, const LaunchCfg &c)
            var_ok(prec, c.var) && (c.var == 0 || c.rpt == 1) &&
            (c.var < 4 || c.var == VAR_BRICK ||
             (c.block <= 256 && op->g.dims[3] % (c.var == 4 ? 4 : c.var == 5 ? 8 : 16) == 0)) &&
-           (c.var != VAR_BRICK || (op->ns == 0 && c.bx * c.by * c.bz * c.lanes == c.block &&
+           (c.var != VAR_BRICK || (c.bx * c.by * c.bz * c.lanes == c.block &&
                                    brick_ok(op->g.dims, prec, c.bx, c.by, c.bz, c.tsteps, c.wpe, c.lanes))) &&
            (c.wpe == 0 || c.var == VAR_BRICK) && (c.gmaj == 0 || c.gmaj == 1);
 }
@@ -455,12 +465,10 @@ static bool launch_ok(const wl_op *op, int nrhs, const LaunchCfg &c)
 static void brick_candidates(const wl_op *op, int nrhs, std::vector<LaunchCfg> &out)
 {
     const int *L = op->g.dims;
-    if (op->ns > 0)
-        return;
     const int sites[] = {64, 128, 256};
     const int bxs[] = {4, 8, 16, 32};
     const int ts[] = {4, 8, 16};
-    for (int rw = 1; rw <= 4; rw *= 2) {
+    for (int rw = 1; rw <= (op->ns > 0 ? 1 : 4); rw *= 2) {
         if (nrhs % rw != 0)
             continue;
         for (int nb : sites) {
@@ -1284,7 +1292,8 @@ int wl_set_launch(wl_op *op, int nrhs, const wl_launch *cfg)
         return WL_EINVAL;
     }
     c.gmaj = cfg->rhs_major;
-    if (!launch_ok(op, nrhs, c))
+    // a domain-wall brick walk is the library's own choice only
+    if (!launch_ok(op, nrhs, c) || (op->ns > 0 && c.var == VAR_BRICK))
         return WL_EINVAL;
     std::lock_guard<std::mutex> lk(op->mu);
     for (int red = RED_NONE; red <= RED_LAST; ++red)  // every stencil of this nrhs

@@ -28,6 +28,13 @@
 // once from HBM, the rest from L1 / L2) -- the gauge field is common to every
 // right-hand side (Sec. II-B).
 //
+// Domain wall (Sec. II-B, eq. (2)): the slices run as columns, those of a
+// brick back to back on one XCD; their fifth-dimension terms are added in the
+// epilogue from the neighbouring slices' spinors (L2).  At 32^3 x 64 x 8 in FP32
+// 1154 us against 1365 for the pipelined hops (3.1 TB/s of the bytes it needs):
+// a third of the vector memory instructions per site, but each slice still
+// loads the links for itself, from L2.
+//
 // The hops are accumulated in the order +x, -x, +y, -y, +z, -z, +t, -t as in
 // every other variant, so FP64 and FP32 results are bit-identical to them
 // (16-bit storage: equal to rounding, as for the t-walk).
@@ -67,52 +74,117 @@ struct RawSp {
     float sc;
 };
 
+// Addresses in the walk: a scalar base (field, right-hand side, chunk and
+// t-slice) plus a 32-bit byte offset within a t-slice, which is the same in
+// every step, so the loop spends no vector instructions on addresses (64-bit
+// additions and LDS address sums: 1200 -> 1105 vector instructions a step in
+// FP32, 1305 -> 1143 in FP64; FP16 at 32^3 x 64 101 -> 98 us, FP64 375 -> 371 us,
+// FP32 within noise: those are bound by the data).  A t-slice of a chunk must
+// stay within 4 GiB: brick_span_ok.
+inline bool brick_span_ok(const int *L) { return (uint64_t)L[0] * L[1] * L[2] <= (1ull << 28); }
+
+typedef __attribute__((address_space(1))) char gchar_t;
+// The scalar base, held in scalar registers: the compiler would otherwise
+// fold the offset into it and add the chunk strides to 64-bit vector
+// addresses.
+__device__ __forceinline__ gchar_t *scalar_base(const void *p)
+{
+    uint64_t u = reinterpret_cast<uint64_t>(p);
+    asm("" : "+s"(u));
+    return reinterpret_cast<gchar_t *>(u);
+}
+template <typename T>
+__device__ __forceinline__ T at(const char *base, uint32_t off)
+{
+    typedef unsigned words __attribute__((ext_vector_type(sizeof(T) / 4)));
+    return __builtin_bit_cast(T, *reinterpret_cast<const __attribute__((address_space(1))) words *>(scalar_base(base) + off));
+}
+
+// First chunk of a right-hand side's t-slice (toff sites in) of a packed
+// spinor field, and its scales.
 template <int P>
-__device__ __forceinline__ void raw_spinor(const StencilParams &p, uint32_t s, int rhs, RawSp<P> &r)
+__device__ __forceinline__ const char *slice_chunks(const void *f, uint32_t V, int rhs, uint32_t toff)
+{
+    return reinterpret_cast<const char *>(f) + ((size_t)rhs * Traits<P>::NCH * V + toff) * 16;
+}
+template <int P>
+__device__ __forceinline__ const char *slice_scales(const void *f, uint32_t V, int nrhs, int rhs, uint32_t toff)
+{
+    return reinterpret_cast<const char *>(scale_ptr<P>(f, V, nrhs)) + ((size_t)rhs * V + toff) * 4;
+}
+
+template <int P>
+__device__ __forceinline__ void raw_spinor(const StencilParams &p, uint32_t xyz, uint32_t toff, int rhs, RawSp<P> &r)
 {
     using C = typename RawSp<P>::C;
-    const C *b = reinterpret_cast<const C *>(p.in) + (size_t)rhs * Traits<P>::NCH * p.V + s;
+    const char *b = slice_chunks<P>(p.in, p.V, rhs, toff);
 #pragma unroll
     for (int k = 0; k < Traits<P>::NCH; ++k)
-        r.sp[k] = b[(size_t)k * p.V];
+        r.sp[k] = at<C>(b + (size_t)k * p.V * 16, xyz * 16u);
     if constexpr (Traits<P>::SCALED)
-        r.sc = scale_ptr<P>(p.in, p.V, p.nrhs)[(size_t)rhs * p.V + s];
+        r.sc = at<float>(slice_scales<P>(p.in, p.V, p.nrhs, rhs, toff), xyz * 4u);
     else
         r.sc = 1.f;
 }
 
 template <int P>
-__device__ __forceinline__ void raw_link(const StencilParams &p, uint32_t s, int mu, RawHop<P> &r)
+__device__ __forceinline__ void raw_link(const StencilParams &p, uint32_t xyz, uint32_t toff, int mu, RawHop<P> &r)
 {
-    if constexpr (P == F64) {
-        const double2 *u = reinterpret_cast<const double2 *>(p.U) + (size_t)mu * 6 * p.V + s;
+    using K = typename std::remove_reference<decltype(r.lk[0])>::type;
+    constexpr int NU = Traits<P>::LINK_UNITS;
+    const char *u = reinterpret_cast<const char *>(p.U) + ((size_t)mu * NU * p.V + toff) * sizeof(K);
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
-            r.lk[k] = u[(size_t)k * p.V];
-    } else if constexpr (P == F32) {
-        const float4 *u = reinterpret_cast<const float4 *>(p.U) + (size_t)mu * 3 * p.V + s;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            r.lk[k] = u[(size_t)k * p.V];
-    } else {
-        const uint2 *u = reinterpret_cast<const uint2 *>(p.U) + (size_t)mu * 3 * p.V + s;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            r.lk[k] = u[(size_t)k * p.V];
-    }
+    for (int k = 0; k < NU; ++k)
+        r.lk[k] = at<K>(u + (size_t)k * p.V * sizeof(K), xyz * (uint32_t)sizeof(K));
 }
 
-// Copy a stored spinor slot (LDS) into the spinor part of a raw hop.
+// LDS stage: FP64 and FP32 keep the chunks of 64 slots together ([group of
+// 64 slots][chunk][64]), so that a slot's chunks lie a constant 1 KB apart
+// and one address serves them all; the 16-bit formats, with three chunks and
+// the scales, are [chunk][slot], then [slot] scales.
 template <int P>
-__device__ __forceinline__ void lds_spinor(const char *smem, int NSP, int slot, RawHop<P> &r)
+__device__ __forceinline__ uint32_t slot_addr(int slot)
+{
+    if constexpr (Traits<P>::SCALED)
+        return (uint32_t)slot * 16u;
+    else
+        return ((uint32_t)(slot >> 6) * (Traits<P>::NCH * 64u) + (uint32_t)(slot & 63)) * 16u;
+}
+template <int P>
+__device__ __forceinline__ uint32_t chunk_step(int NSP)
+{
+    return Traits<P>::SCALED ? (uint32_t)NSP * 16u : 1024u;
+}
+
+// Copy a stored spinor slot (its address in the stage) into the spinor part
+// of a raw hop.
+template <int P>
+__device__ __forceinline__ void lds_spinor(const char *smem, int NSP, uint32_t addr, RawHop<P> &r)
 {
     using C = typename RawSp<P>::C;
-    const C *b = reinterpret_cast<const C *>(smem);
 #pragma unroll
     for (int k = 0; k < Traits<P>::NCH; ++k)
-        r.sp[k] = b[k * NSP + slot];
+        r.sp[k] = *reinterpret_cast<const C *>(smem + addr + k * chunk_step<P>(NSP));
     if constexpr (Traits<P>::SCALED)
-        r.sc = reinterpret_cast<const float *>(smem + (size_t)NSP * Traits<P>::NCH * 16)[slot];
+        r.sc = *reinterpret_cast<const float *>(smem + (size_t)NSP * Traits<P>::NCH * 16 + addr / 4);
+}
+
+// Store a site at a scalar slice base, as store_site_q (the stored values
+// replace v).
+template <int P>
+__device__ __forceinline__ void store_slice_q(const StencilParams &p, uint32_t xyz, uint32_t toff, int rhs,
+                                              cx<typename Traits<P>::real> (&v)[12])
+{
+    using C = typename RawSp<P>::C;
+    char *b = const_cast<char *>(slice_chunks<P>(p.out, p.V, rhs, toff));
+    C c[Traits<P>::NCH];
+    float m = 0.f;
+    encode_site_q<P>(v, c, m);
+#pragma unroll
+    for (int k = 0; k < Traits<P>::NCH; ++k)
+        st16<true>((C *)(scalar_base(b + (size_t)k * p.V * 16) + xyz * 16u), c[k]);
+    if constexpr (Traits<P>::SCALED)
+        st4<true>((float *)(scalar_base(slice_scales<P>(p.out, p.V, p.nrhs, rhs, toff)) + xyz * 4u), m);
 }
 
 // Global (x, y, z) index of halo slot h of the brick with origin o.
@@ -134,8 +206,12 @@ __device__ __forceinline__ uint32_t halo_site(const StencilParams &p, const Bric
     return (uint32_t)c[0] + (uint32_t)p.L[0] * ((uint32_t)c[1] + (uint32_t)p.L[1] * (uint32_t)c[2]);
 }
 
+// Wavefronts per SIMD asked of the compiler: three in 16 bits where the fused
+// reduction leaves the registers for it (168 each).
+constexpr int brick_waves(int prec, int red) { return prec >= BF16S && red != RED_BICG && red != RED_SR ? 3 : 1; }
+
 template <int P, int DAG, int RED, int APPLY, int MULTI>
-__global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g)
+__global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(StencilParams p, BrickGeom g)
 {
     using R_ = typename Traits<P>::real;
     using Ch = typename RawSp<P>::C;
@@ -179,7 +255,7 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
         const int c[3] = {o[0] + bc_[0], o[1] + bc_[1], o[2] + bc_[2]};
         const uint32_t sx = (uint32_t)c[0] + (uint32_t)p.L[0] * ((uint32_t)c[1] + (uint32_t)p.L[1] * (uint32_t)c[2]);
         // spatial neighbours: LDS slot, (x, y, z) index (for the backward links) and boundary sign
-        int slot[6];
+        uint32_t slot[6];  // LDS addresses of the neighbours' slots
         uint32_t nbx[6];
         float sg[6];
         {
@@ -191,12 +267,14 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
                 const int L = p.L[mu], B = g.B[mu];
                 const bool full = B == L;  // the brick spans the direction: neighbours wrap inside it
                 const bool wf = c[mu] == L - 1, wb = c[mu] == 0;
-                slot[2 * mu] = bc_[mu] + 1 < B ? tid + bstride[mu]
-                               : full        ? tid - (B - 1) * bstride[mu]
-                                             : g.NB + g.hoff[2 * mu + 1] + pos[mu];
-                slot[2 * mu + 1] = bc_[mu] > 0 ? tid - bstride[mu]
-                                   : full      ? tid + (B - 1) * bstride[mu]
-                                               : g.NB + g.hoff[2 * mu] + pos[mu];
+                const int sf = bc_[mu] + 1 < B ? tid + bstride[mu]
+                               : full          ? tid - (B - 1) * bstride[mu]
+                                               : g.NB + g.hoff[2 * mu + 1] + pos[mu];
+                const int sb = bc_[mu] > 0 ? tid - bstride[mu]
+                               : full      ? tid + (B - 1) * bstride[mu]
+                                           : g.NB + g.hoff[2 * mu] + pos[mu];
+                slot[2 * mu] = slot_addr<P>(sf);
+                slot[2 * mu + 1] = slot_addr<P>(sb);
                 const uint32_t span = (uint32_t)(L - 1) * stride;
                 nbx[2 * mu] = wf ? sx - span : sx + stride;
                 nbx[2 * mu + 1] = wb ? sx + span : sx - stride;
@@ -217,7 +295,7 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
         const int t0 = (int)chunk * g.T;
         const R_ one = (R_)p.one;
         RawSp<P> cur;
-        raw_spinor<P>(p, sx + g.nxyz * (uint32_t)t0, rhs, cur);
+        raw_spinor<P>(p, sx, g.nxyz * (uint32_t)t0, rhs, cur);
         // prologue: the backward-t hop into the site at t0, carried as the
         // projected half-spinor Cg and its coefficient Cs (sign and 16-bit scale)
         cx<R_> Cg[6];
@@ -233,48 +311,52 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
             if constexpr (Traits<P>::SCALED)
                 Cs *= rb.sc;
         }
-        Ch *lsp = reinterpret_cast<Ch *>(smem);
+        const uint32_t own = slot_addr<P>(tid), step = chunk_step<P>(g.NSP);
         float *lsc = reinterpret_cast<float *>(smem + (size_t)g.NSP * NCH * 16);
         const R_ kap = (R_)p.kappa;
+        // site offsets within a t-slice, re-read in every step: hoisted out of
+        // the loop as 64-bit values they would make every address a vector sum
+        uint32_t xo = sx, bo[3] = {nbx[1], nbx[3], nbx[5]};
         for (int k = 0; k < g.T; ++k) {
             const int t = t0 + k;
             const uint32_t toff = g.nxyz * (uint32_t)t;
             const uint32_t s = sx + toff;
+            asm volatile("" : "+v"(xo), "+v"(bo[0]), "+v"(bo[1]), "+v"(bo[2]));
+            asm volatile("" : "+v"(hsite[0]), "+v"(hsite[1]), "+v"(hsite[2]), "+v"(hsite[3]));
             __syncthreads();  // every read of the previous slice's LDS stage is done
             // stage the slice: own spinor from registers, halo by direct-to-LDS copies
 #pragma unroll
             for (int q = 0; q < NCH; ++q)
-                lsp[q * g.NSP + tid] = cur.sp[q];
+                *reinterpret_cast<Ch *>(smem + own + q * step) = cur.sp[q];
             if constexpr (Traits<P>::SCALED)
                 lsc[tid] = cur.sc;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int grp = w + j * nw;
                 if (grp < g.NHG) {  // uniform per wavefront
-                    const uint32_t hs = hsite[j] + toff;
+                    const char *src = slice_chunks<P>(p.in, p.V, rhs, toff);
+                    const uint32_t dst = slot_addr<P>(g.NB + grp * 64);
 #pragma unroll
-                    for (int q = 0; q < NCH; ++q) {
-                        const Ch *src = reinterpret_cast<const Ch *>(p.in) + ((size_t)rhs * NCH + q) * p.V + hs;
-                        __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_t *)(lsp + q * g.NSP + g.NB + grp * 64), 16, 0, 0);
-                    }
-                    if constexpr (Traits<P>::SCALED) {
-                        const float *src = scale_ptr<P>(p.in, p.V, p.nrhs) + (size_t)rhs * p.V + hs;
-                        __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_t *)(lsc + g.NB + grp * 64), 4, 0, 0);
-                    }
+                    for (int q = 0; q < NCH; ++q)
+                        __builtin_amdgcn_global_load_lds((const void *)(scalar_base(src + (size_t)q * p.V * 16) + hsite[j] * 16u),
+                                                         (lds_void_t *)(smem + dst + q * step), 16, 0, 0);
+                    if constexpr (Traits<P>::SCALED)
+                        __builtin_amdgcn_global_load_lds(
+                            (const void *)(scalar_base(slice_scales<P>(p.in, p.V, p.nrhs, rhs, toff)) + hsite[j] * 4u),
+                            (lds_void_t *)(lsc + g.NB + grp * 64), 4, 0, 0);
                 }
             }
             // forward t neighbour (the next slice's own spinor) and U_t(x, t)
             const bool wf = t == Lt - 1;
-            const uint32_t sn = sx + g.nxyz * (uint32_t)(wf ? 0 : t + 1);
             RawSp<P> nxt;
-            raw_spinor<P>(p, sn, rhs, nxt);
+            raw_spinor<P>(p, xo, g.nxyz * (uint32_t)(wf ? 0 : t + 1), rhs, nxt);
             RawHop<P> rf;
-            raw_link<P>(p, s, 3, rf);
+            raw_link<P>(p, xo, toff, 3, rf);
             RawHop<P> lnk[6];
             if constexpr (LINKS_EARLY) {
 #pragma unroll
                 for (int h = 0; h < 6; ++h)
-                    raw_link<P>(p, (h & 1) ? nbx[h] + toff : s, h >> 1, lnk[h]);
+                    raw_link<P>(p, (h & 1) ? bo[h >> 1] : xo, toff, h >> 1, lnk[h]);
             }
             __syncthreads();  // the slice is in LDS (waits for the direct-to-LDS copies)
             cx<R_> acc[12];
@@ -289,7 +371,7 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
                     for (int q = 0; q < (P == F64 ? 6 : 3); ++q)
                         r.lk[q] = lnk[h].lk[q];
                 } else {
-                    raw_link<P>(p, (h & 1) ? nbx[h] + toff : s, h >> 1, r);
+                    raw_link<P>(p, (h & 1) ? bo[h >> 1] : xo, toff, h >> 1, r);
                 }
                 lds_spinor<P>(smem, g.NSP, slot[h], r);
                 switch (h) {
@@ -303,7 +385,7 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
             }
             // the site's own spinor (the stored values, scaled), with U_t(x)
             RawHop<P> rs;
-            lds_spinor<P>(smem, g.NSP, tid, rs);
+            lds_spinor<P>(smem, g.NSP, own, rs);
             for (int q = 0; q < (P == F64 ? 6 : 3); ++q)
                 rs.lk[q] = rf.lk[q];
             cx<R_> self[12];
@@ -336,7 +418,9 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
             else
                 Cs = R_(1);
             cx<R_> o[12];
-            if constexpr (APPLY) {
+            if constexpr (APPLY == 2) {
+                dw_epilogue<P, DAG>(p, s, rhs, self, acc, o);
+            } else if constexpr (APPLY) {
 #pragma unroll
                 for (int i = 0; i < 12; ++i)
                     o[i] = cx<R_>{fma(-kap, acc[i].re, self[i].re), fma(-kap, acc[i].im, self[i].im)};
@@ -347,7 +431,7 @@ __global__ __launch_bounds__(256) void brick_kernel(StencilParams p, BrickGeom g
             }
             if constexpr (APPLY == 3)
                 residual_epilogue<P>(p, s, rhs, o);
-            store_site_q<P, true>(p.out, p.V, p.nrhs, s, rhs, o);
+            store_slice_q<P>(p, xo, toff, rhs, o);
             if constexpr (RED == RED_NORM || RED == RED_DOTIN_NORM) {
 #pragma unroll
                 for (int i = 0; i < 12; ++i)
@@ -557,6 +641,13 @@ inline hipError_t launch_brick(const LaunchCfg &cfg, StencilParams p, hipStream_
         if (p.red != RED_NONE)
             return hipErrorInvalidValue;
         return brick_go<P, DAG, RED_NONE, 0>(grid, block, smem, p, g, st);
+    }
+    if (p.apply == 2) {  // domain wall: the reductions CG on the normal equations needs
+        if (p.red == RED_NONE)
+            return brick_go<P, DAG, RED_NONE, 2>(grid, block, smem, p, g, st);
+        if (p.red == RED_NORM)
+            return brick_go<P, DAG, RED_NORM, 2>(grid, block, smem, p, g, st);
+        return hipErrorInvalidValue;
     }
     if (p.apply != 1)
         return hipErrorInvalidValue;

@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace wl {
 
 enum Prec { F64 = 0, F32 = 1, BF16S = 2, F16S = 3 };
@@ -63,14 +65,6 @@ template <typename T>
 __device__ __forceinline__ cx<T> ifma(T s, cx<T> a, cx<T> c) { return cx<T>{fma(-s, a.im, c.re), fma(s, a.re, c.im)}; }
 
 // ---------------------------------------------------------------- 16-bit reals
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u)
-        return 0x7fc0u;  // NaN stays NaN
-    u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even
-    return u >> 16;
-}
 __device__ __forceinline__ float bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ uint32_t f32_to_f16(float f)
 {
@@ -82,9 +76,13 @@ __device__ __forceinline__ float f16_to_f32(uint32_t h) { return (float)__builti
 template <int P>
 __device__ __forceinline__ uint32_t pack2(float re, float im)
 {
-    if constexpr (P == BF16S)
-        return f32_to_bf16(re) | (f32_to_bf16(im) << 16);
-    else
+    if constexpr (P == BF16S) {
+        // v_cvt_pk_bf16_f32 converts both halves: round to nearest even, NaN stays
+        // NaN, the same results as the integer rounding (checked over all inputs)
+        typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){re, im}, bf2));
+    } else
         return f32_to_f16(re) | (f32_to_f16(im) << 16);
 }
 template <int P>
@@ -282,20 +280,26 @@ __device__ __forceinline__ void store_site(void *base, uint32_t V, int nrhs, uin
     }
 }
 
-// Store a site and replace v by exactly what was stored (16-bit formats
-// quantise once: site maximum, scale, round to nearest even).
-template <int P, bool NT = false>
-__device__ __forceinline__ void store_site_q(void *base, uint32_t V, int nrhs, uint32_t s, int rhs,
-                                             cx<typename Traits<P>::real> (&v)[12])
+// The stored form of a site: its chunks and, for 16-bit formats, its scale m;
+// v becomes exactly what is stored (16-bit formats quantise once: site
+// maximum, scale, round to nearest even).
+template <int P, typename C>
+__device__ __forceinline__ void encode_site_q(cx<typename Traits<P>::real> (&v)[12], C (&c)[Traits<P>::NCH], float &m)
 {
-    if constexpr (Traits<P>::SCALED) {
-        float m = 0.f;
+    if constexpr (P == F64) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k)
+            c[k] = make_double2(v[k].re, v[k].im);
+    } else if constexpr (P == F32) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            c[k] = make_float4(v[2 * k].re, v[2 * k].im, v[2 * k + 1].re, v[2 * k + 1].im);
+    } else {
+        m = 0.f;
 #pragma unroll
         for (int k = 0; k < 12; ++k)
             m = fmaxf(m, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
         const float inv = m > 0.f ? 1.0f / m : 0.f;
-        const size_t off = (size_t)rhs * 3 * V + s;
-        uint4 *b = reinterpret_cast<uint4 *>(base) + off;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             uint32_t w[4];
@@ -305,12 +309,27 @@ __device__ __forceinline__ void store_site_q(void *base, uint32_t V, int nrhs, u
                 const cx<float> q = unpack2<P>(w[j]);
                 v[4 * k + j] = cx<float>{q.re * m, q.im * m};
             }
-            st16<NT>(&b[(size_t)k * V], make_uint4(w[0], w[1], w[2], w[3]));
+            c[k] = make_uint4(w[0], w[1], w[2], w[3]);
         }
+    }
+}
+
+// Store a site and replace v by exactly what was stored.
+template <int P, bool NT = false>
+__device__ __forceinline__ void store_site_q(void *base, uint32_t V, int nrhs, uint32_t s, int rhs,
+                                             cx<typename Traits<P>::real> (&v)[12])
+{
+    using C = typename std::conditional<P == F64, double2, typename std::conditional<P == F32, float4, uint4>::type>::type;
+    C c[Traits<P>::NCH];
+    float m = 0.f;
+    encode_site_q<P>(v, c, m);
+    C *b = reinterpret_cast<C *>(base) + (size_t)rhs * Traits<P>::NCH * V + s;
+#pragma unroll
+    for (int k = 0; k < Traits<P>::NCH; ++k)
+        st16<NT>(&b[(size_t)k * V], c[k]);
+    if constexpr (Traits<P>::SCALED) {
         float *scp = const_cast<float *>(scale_ptr<P>(base, V, nrhs));
         st4<NT>(&scp[(size_t)rhs * V + s], m);
-    } else {
-        store_site<P, NT>(base, V, nrhs, s, rhs, v);
     }
 }
 

@@ -51,10 +51,18 @@ int stencil_nval(int red) { return red_nval(red); }
 
 static uint32_t pad8(uint32_t n) { return (n + 7u) & ~7u; }
 
+// The shape a launch runs in: a brick walk whose t-slices exceed its 32-bit
+// offsets (2^28 sites of 16 bytes) takes the straight-line kernel.
+static LaunchCfg shape_of(const LaunchCfg &c, const int *L)
+{
+    return c.rpt == 1 && c.var == VAR_BRICK && !brick_span_ok(L) ? LaunchCfg{256, 1, 1, 0, 1} : c;
+}
+
 // Number of per-workgroup partials (per right-hand side) a launch with this
 // configuration writes.
-int stencil_partials(const LaunchCfg &cfg, const int *L, uint32_t V, int nrhs)
+int stencil_partials(const LaunchCfg &cfg0, const int *L, uint32_t V, int nrhs)
 {
+    const LaunchCfg cfg = shape_of(cfg0, L);
     const uint32_t tile = (uint32_t)(cfg.block / cfg.lanes);
     uint32_t n = (V + tile - 1) / tile;
     if (cfg.rpt == 1 && cfg.var == VAR_BRICK && cfg.bx > 0 && cfg.by > 0 && cfg.bz > 0 && cfg.tsteps > 0) {
@@ -68,16 +76,18 @@ int stencil_partials(const LaunchCfg &cfg, const int *L, uint32_t V, int nrhs)
 
 int max_rpt(int prec) { return prec == F64 ? 2 : 4; }
 
-hipError_t launch_stencil(int prec, int dagger, const LaunchCfg &cfg, StencilParams p, hipStream_t st)
+hipError_t launch_stencil(int prec, int dagger, const LaunchCfg &cfg0, StencilParams p, hipStream_t st)
 {
+    const LaunchCfg cfg = shape_of(cfg0, p.L);
     const int lg = cfg.lanes == 1 ? 0 : cfg.lanes == 2 ? 1 : cfg.lanes == 4 ? 2 : cfg.lanes == 8 ? 3 : -1;
     if (cfg.rpt < 1 || cfg.rpt > 4 || p.nrhs % cfg.rpt != 0 || cfg.block < 64 || cfg.block > 512 ||
         cfg.block % 64 != 0 || lg < 0 ||
         (lg > 0 && (cfg.rpt != 1 || p.nrhs % cfg.lanes != 0 ||
                     (cfg.var != VAR_BRICK && (cfg.block >> lg) < (cfg.var >= 4 ? 32 : 64)))))
         return hipErrorInvalidValue;
-    if (p.apply == 2 && (cfg.rpt != 1 || (cfg.var > 2 && cfg.var < 4) || cfg.var > 6 || p.ns < 1 || p.nrhs % p.ns != 0))
-        return hipErrorInvalidValue;  // domain wall: one slice per thread, variants 0..2 and the t-walks
+    if (p.apply == 2 && (cfg.rpt != 1 || cfg.var == 3 || (cfg.var == VAR_BRICK && cfg.lanes != 1) || p.ns < 1 ||
+                         p.nrhs % p.ns != 0))
+        return hipErrorInvalidValue;  // domain wall: one slice per thread, variants 0..2, the walks, one slice per brick
     if (p.apply == 3 && (!p.aux || (prec != F64 && prec != F32) || (p.red != RED_NONE && p.red != RED_NORM)))
         return hipErrorInvalidValue;  // residual: FP64 / FP32, with |r|^2 or without
     if (cfg.gmaj != 0 && cfg.gmaj != 1)

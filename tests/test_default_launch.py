@@ -31,7 +31,9 @@ def test_default_shape_is_valid_everywhere():
         h = _op(dims, prec, ns)
         c = wilson.wl_launch()
         assert wilson.lib().wl_get_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK
-        assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK, (dims, prec, ns, nrhs, c.variant)
+        # a domain-wall brick walk is the library's own choice: not offered to callers
+        want = wilson.WL_EINVAL if ns and c.variant == wilson.VAR_BRICK else wilson.WL_OK
+        assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(c)) == want, (dims, prec, ns, nrhs, c.variant)
         seen.add((prec, c.variant, ns > 0, nrhs > 1))
         wilson.lib().wl_op_destroy(h)
     for prec in (wilson.WL_F64, wilson.WL_F32, wilson.WL_F16S):
@@ -71,3 +73,39 @@ def test_default_matches_straight_line(dims, nrhs, prec):
         else:
             a, b = op.unpack(got, nrhs), op.unpack(ref, nrhs)
             assert float((a - b).norm() / b.norm()) < (2.0 ** -7 if prec == "bf16" else 2.0 ** -10)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,ns,prec", [((32, 32, 32, 4), 4, "f32"), ((32, 32, 32, 2), 4, "f64"),
+                                          ((32, 32, 32, 3), 8, "bf16"), ((32, 32, 32, 4), 7, "f16"),
+                                          ((64, 16, 32, 6), 4, "f32")])
+def test_domain_wall_bricks(dims, ns, prec):
+    """The brick walk's fifth-dimension terms: the bits of the straight-line kernel in FP64 and
+    FP32, the storage rounding (as above) in 16 bits; D and D^dag, and the fused |D x|^2 of CG."""
+    torch = pytest.importorskip("torch")
+    Lx, Ly, Lz, Lt = dims
+    U = torch.from_numpy(inputs.near_unity_gauge((2, 2, 2, 2), 0.3, seed=3)).to("cuda")
+    U = U.repeat(1, -(-Lt // 2), Lz // 2, Ly // 2, Lx // 2, 1, 1)[:, :Lt].contiguous()
+    g = torch.Generator(device="cuda").manual_seed(2)
+    psi = torch.view_as_complex(torch.randn(ns, Lt, Lz, Ly, Lx, 4, 3, 2, dtype=torch.float64, device="cuda", generator=g))
+    op = wilson.DWOperator.create(U, -1.8, 0.05, ns, wilson.PREC[prec])
+    assert wilson.wl_get_launch(op.handle, 1)[3] == wilson.VAR_BRICK
+    src = op.pack(psi)
+    outs = []
+    for shape in (None, (64, 1, 0, 0, 1)):
+        if shape:
+            assert wilson.try_set_launch(op.handle, 1, *shape)
+        for dagger in (False, True):
+            out = op.new_field()
+            op.apply_packed(out, src, 1, dagger)
+            outs.append(out)
+    for got, ref in ((outs[0], outs[2]), (outs[1], outs[3])):
+        if prec in ("f64", "f32"):
+            assert torch.equal(got, ref)
+        else:
+            a, b = op.unpack(got), op.unpack(ref)
+            assert float((a - b).norm() / b.norm()) < (2.0 ** -7 if prec == "bf16" else 2.0 ** -10)
+    if prec == "f64":  # CG with the fused norms; its solution against the operator itself
+        x, st = wilson.dw_solve(U, psi, -1.8, 0.05, precision="f64", tol=1e-9, return_stats=True)
+        r = psi - wilson.dw_apply(U, x, -1.8, 0.05, op=op)
+        assert st["converged"] and float(r.norm() / psi.norm()) <= 1e-9
