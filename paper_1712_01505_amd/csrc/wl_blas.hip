@@ -66,7 +66,403 @@ __host__ __device__ constexpr int blas_nv(int op)
 }
 __host__ __device__ constexpr int blas_spt(int op) { return op == B_SR_PV ? 4 : 1; }
 
-template <int P, int OP>
+__device__ __forceinline__ bool finite2(double a) { return isfinite(a); }
+__device__ __forceinline__ double2 cmul(double2 a, double2 b)
+{
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+__device__ __forceinline__ double2 cdiv(double2 a, double2 b)  // b != 0
+{
+    const double d = b.x * b.x + b.y * b.y;
+    return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
+}
+
+// One scalar step of a column: the sums of the partial sets A, B, C (value k
+// at [k * st]; null where the step has none) advance sc.
+__device__ __forceinline__ void scalar_step(int op, Scalars &sc, const double *A, const double *B, const double *C, int st,
+                                            int iter, double tol2)
+{
+    const double2 zero = make_double2(0.0, 0.0), one = make_double2(1.0, 0.0);
+    switch (op) {
+    case F_INIT_CG: {
+        sc.rr = A[0];
+        sc.zz = B ? B[0] : 0.0;  // the single-reduction form computes z in its loop
+        sc.bb = C[0];
+        sc.rr_upd = sc.rr;
+        sc.restart = 0;
+        sc.tol2 = tol2;
+        sc.alpha = sc.beta = zero;
+        sc.flag = 0;
+        sc.conv_iter = 0;
+        if (!finite2(sc.rr) || !finite2(sc.zz) || !finite2(sc.bb))
+            sc.flag = 3;
+        else if (sc.rr <= sc.tol2 * sc.bb)
+            sc.flag = 1;
+        sc.frozen = sc.flag != 0;
+        break;
+    }
+    case F_CG_ALPHA: {
+        const double ww = A[0];
+        if (sc.flag == 0) {
+            if (!finite2(ww))
+                sc.flag = 3;
+            else if (ww > 0.0) {
+                sc.alpha = make_double2(sc.zz / ww, 0.0);
+                break;
+            } else
+                sc.flag = 2;
+        }
+        sc.alpha = zero;
+        break;
+    }
+    case F_CG_BETA: {
+        const double rr = A[0], zz = B[0];
+        if (sc.flag == 0) {
+            sc.rr = rr;
+            if (!finite2(rr) || !finite2(zz))
+                sc.flag = 3;
+            else if (rr <= sc.tol2 * sc.bb) {
+                sc.flag = 1;
+                sc.conv_iter = iter + 1;
+            } else if (sc.zz > 0.0) {
+                sc.beta = make_double2(zz / sc.zz, 0.0);
+                sc.zz = zz;
+                break;
+            } else
+                sc.flag = 2;
+        }
+        sc.beta = zero;
+        sc.frozen = 1;  // end of the iteration with flag != 0
+        break;
+    }
+    case F_CG_RELIABLE: {
+        // r was replaced by the (converted) true residual and z = D^dag r
+        // recomputed; the search direction is kept
+        if (sc.flag == 0) {
+            const double rr = A[0], zz = B[0];
+            sc.rr = rr;
+            if (!finite2(rr) || !finite2(zz))
+                sc.flag = 3;
+            else if (rr <= sc.tol2 * sc.bb) {
+                sc.flag = 1;
+                sc.conv_iter = iter + 1;
+            } else if (zz > 0.0) {
+                sc.zz = zz;
+                // |r| has grown since the previous update: the low-precision
+                // recurrence has lost its search space; start it again from z
+                sc.restart = rr > sc.rr_upd;
+                sc.rr_upd = rr;
+            } else
+                sc.flag = 2;
+            if (sc.flag != 0) {
+                sc.alpha = sc.beta = zero;
+                sc.frozen = 1;
+            }
+        }
+        break;
+    }
+    case F_INIT_BI: {
+        sc.rr = A[0];
+        sc.bb = C[0];
+        sc.tol2 = tol2;
+        sc.rho = make_double2(sc.rr, 0.0);
+        sc.rho_prev = sc.rho;  // <rh, r0> with rh = r0
+        sc.alpha = sc.omega = one;
+        sc.beta = zero;  // p = v = 0 -> first p = r
+        sc.brk = 0;
+        sc.flag = 0;
+        sc.conv_iter = 0;
+        if (!finite2(sc.rr) || !finite2(sc.bb))
+            sc.flag = 3;
+        else if (sc.rr <= sc.tol2 * sc.bb)
+            sc.flag = 1;
+        sc.frozen = sc.flag != 0;
+        break;
+    }
+    case F_BI_ALPHA: {
+        const double2 rv = make_double2(A[0], A[st]);
+        if (sc.flag == 0) {
+            const double d = rv.x * rv.x + rv.y * rv.y;
+            if (!finite2(d))
+                sc.flag = 3;
+            else if (d > 0.0) {  // alpha = rho / <rh, v>
+                sc.alpha = make_double2((sc.rho.x * rv.x + sc.rho.y * rv.y) / d, (sc.rho.y * rv.x - sc.rho.x * rv.y) / d);
+                break;
+            } else
+                sc.flag = 2;
+        }
+        sc.alpha = zero;
+        break;
+    }
+    case F_BI_OMEGA_RHO: {
+        // omega = <t, s> / <t, t> (or stop: converged on |s|, t = 0, NaN);
+        // then, with r' = s - omega t still to be formed,
+        // rho' = <rh, r'> = <rh, s> - omega <rh, t> and beta = (rho'/rho)(alpha/omega)
+        const double ss = A[7 * st];
+        const double st_re = A[0], st_im = A[st], tt = A[2 * st];
+        const double2 hs = make_double2(A[3 * st], A[4 * st]);
+        const double2 ht = make_double2(A[5 * st], A[6 * st]);
+        sc.ss = ss;
+        sc.brk = 0;
+        sc.beta = zero;
+        if (sc.flag == 0) {
+            if (!finite2(ss) || !finite2(tt) || !finite2(st_re) || !finite2(st_im))
+                sc.flag = 3;
+            else if (ss <= sc.tol2 * sc.bb) {  // x += alpha p ; r = s  (omega = 0)
+                sc.flag = 1;
+                sc.conv_iter = iter + 1;
+            } else if (tt > 0.0) {
+                const double2 om = make_double2(st_re / tt, -st_im / tt);
+                sc.omega = om;
+                const double2 rho_new = make_double2(hs.x - (om.x * ht.x - om.y * ht.y), hs.y - (om.x * ht.y + om.y * ht.x));
+                const double om2 = om.x * om.x + om.y * om.y;
+                const double rho2 = sc.rho.x * sc.rho.x + sc.rho.y * sc.rho.y;
+                if (!finite2(rho_new.x) || !finite2(rho_new.y))
+                    sc.brk = 2;
+                else if (om2 > 0.0 && rho2 > 0.0 && (rho_new.x != 0.0 || rho_new.y != 0.0)) {
+                    const double2 q1 = make_double2((rho_new.x * sc.rho.x + rho_new.y * sc.rho.y) / rho2,
+                                                    (rho_new.y * sc.rho.x - rho_new.x * sc.rho.y) / rho2);
+                    const double2 q2 = make_double2((sc.alpha.x * om.x + sc.alpha.y * om.y) / om2,
+                                                    (sc.alpha.y * om.x - sc.alpha.x * om.y) / om2);
+                    sc.beta = make_double2(q1.x * q2.x - q1.y * q2.y, q1.x * q2.y + q1.y * q2.x);
+                    sc.rho_prev = sc.rho;
+                    sc.rho = rho_new;
+                } else
+                    sc.brk = 1;
+                break;
+            } else
+                sc.flag = 2;
+        } else
+            sc.alpha = zero;
+        sc.omega = zero;
+        break;
+    }
+    case F_BI_CONV: {
+        const double rr = A[0];
+        if (sc.flag == 0) {
+            sc.rr = rr;
+            if (!finite2(rr) || sc.brk == 2)
+                sc.flag = 3;
+            else if (rr <= sc.tol2 * sc.bb) {
+                sc.flag = 1;
+                sc.conv_iter = iter + 1;
+            } else if (sc.brk == 1)
+                sc.flag = 2;
+            else
+                break;
+        } else if (sc.flag == 1 && sc.conv_iter == iter + 1) {
+            sc.rr = rr;  // converged on |s| this iteration: r = s
+        }
+        sc.beta = zero;
+        sc.alpha = zero;
+        sc.omega = zero;
+        sc.frozen = 1;  // end of the iteration with flag != 0
+        break;
+    }
+    case F_CG1: {
+        // CG on the normal equations with one reduction phase per iteration
+        // (Chronopoulos and Gear's form): gamma = |z|^2 with z = D^dag r,
+        // delta = |D z|^2; beta = gamma / gamma_prev and
+        // alpha = gamma / (delta - beta gamma / alpha_prev), where the
+        // denominator equals |D p|^2 for p = z + beta p_prev
+        const double rr = C ? C[0] : sc.rr, gam = A[0], del = B[0];
+        if (sc.flag == 0) {
+            sc.rr = rr;
+            if (!finite2(rr) || !finite2(gam) || !finite2(del))
+                sc.flag = 3;
+            else if (rr <= sc.tol2 * sc.bb) {
+                sc.flag = 1;
+                sc.conv_iter = iter;
+            } else {
+                const double beta = iter > 0 && sc.zz > 0.0 ? gam / sc.zz : 0.0;
+                const double den = beta != 0.0 ? del - beta * gam / sc.alpha.x : del;
+                if (gam > 0.0 && den > 0.0 && finite2(den)) {
+                    sc.alpha = make_double2(gam / den, 0.0);
+                    sc.beta = make_double2(beta, 0.0);
+                    sc.zz = gam;
+                    break;
+                }
+                sc.flag = 2;
+            }
+        }
+        sc.alpha = sc.beta = zero;
+        sc.frozen = 1;  // the update pass of this iteration is skipped
+        break;
+    }
+    case F_SR: {
+        // BiCGStab with one reduction phase per iteration.  With u = D r,
+        // v = D p and q = D v known, s = r - alpha v and t = D s = u - alpha q
+        // never need to be formed before the scalars:
+        //   <t, s> = <u, r> - alpha <u, v> - conj(alpha) <q, r> + |alpha|^2 <q, v>
+        //   <t, t> = |u|^2 - 2 Re(alpha <u, q>) + |alpha|^2 |q|^2
+        //   rho'   = <rh, s> - omega <rh, t>
+        //          = rho - alpha <rh, v> - omega (<rh, u> - alpha <rh, q>)
+        const double rr = C ? C[0] : sc.rr;
+        const double2 hv = make_double2(A[0], A[st]), hu = make_double2(A[2 * st], A[3 * st]);
+        const double2 ur = make_double2(A[4 * st], A[5 * st]), uv = make_double2(A[6 * st], A[7 * st]);
+        const double uu = A[8 * st];
+        const double2 vq = make_double2(B[0], B[st]);
+        const double qq = B[2 * st];
+        const double2 hq = make_double2(B[3 * st], B[4 * st]), rq = make_double2(B[5 * st], B[6 * st]);
+        const double2 uq = make_double2(B[7 * st], B[8 * st]);
+        if (sc.flag == 0) {
+            sc.rr = rr;
+            const double d = hv.x * hv.x + hv.y * hv.y;
+            if (!finite2(rr) || !finite2(d) || !finite2(uu) || !finite2(qq) || sc.brk == 2)
+                sc.flag = 3;
+            else if (rr <= sc.tol2 * sc.bb) {
+                sc.flag = 1;
+                sc.conv_iter = iter;
+            } else if (sc.brk == 1 || !(d > 0.0))
+                sc.flag = 2;
+            if (sc.flag == 0) {
+                const double2 a = cdiv(sc.rho, hv);
+                const double a2 = a.x * a.x + a.y * a.y;
+                // <t, s>
+                const double2 auv = cmul(a, uv);
+                const double2 aqr = cmul(make_double2(a.x, -a.y), make_double2(rq.x, -rq.y));
+                const double2 ts = make_double2(ur.x - auv.x - aqr.x + a2 * vq.x, ur.y - auv.y - aqr.y - a2 * vq.y);
+                const double tt = uu - 2.0 * cmul(a, uq).x + a2 * qq;
+                sc.brk = 0;
+                if (!finite2(ts.x) || !finite2(ts.y) || !finite2(tt)) {
+                    sc.flag = 3;
+                } else if (!(tt > 0.0)) {
+                    sc.flag = 2;
+                } else {
+                    const double2 om = make_double2(ts.x / tt, ts.y / tt);
+                    const double2 ahq = cmul(a, hq);
+                    const double2 w1 = cmul(om, make_double2(hu.x - ahq.x, hu.y - ahq.y));
+                    const double2 ahv = cmul(a, hv);
+                    const double2 rho_new = make_double2(sc.rho.x - ahv.x - w1.x, sc.rho.y - ahv.y - w1.y);
+                    sc.alpha = a;
+                    sc.omega = om;
+                    sc.beta = zero;
+                    if (!finite2(rho_new.x) || !finite2(rho_new.y))
+                        sc.brk = 2;
+                    else if ((om.x != 0.0 || om.y != 0.0) && (rho_new.x != 0.0 || rho_new.y != 0.0))
+                        sc.beta = cmul(cdiv(rho_new, sc.rho), cdiv(a, om));
+                    else
+                        sc.brk = 1;  // this step is taken; the next check reports the breakdown
+                    sc.rho_prev = sc.rho;
+                    sc.rho = rho_new;
+                    break;
+                }
+            }
+        }
+        sc.alpha = sc.beta = sc.omega = zero;
+        sc.frozen = 1;
+        break;
+    }
+    case F_BI_RELIABLE: {
+        // r was just replaced by the (converted) true residual; recompute
+        // rho = <rh, r> and beta = (rho / rho_prev)(alpha / omega) from it
+        if (sc.flag == 0) {
+            const double rr = A[2 * st];
+            const double2 rho_new = make_double2(A[0], A[st]);
+            const double om2 = sc.omega.x * sc.omega.x + sc.omega.y * sc.omega.y;
+            const double rp2 = sc.rho_prev.x * sc.rho_prev.x + sc.rho_prev.y * sc.rho_prev.y;
+            sc.rr = rr;
+            if (!finite2(rr) || !finite2(rho_new.x) || !finite2(rho_new.y)) {
+                sc.flag = 3;
+            } else if (rr <= sc.tol2 * sc.bb) {
+                sc.flag = 1;
+                sc.conv_iter = iter + 1;
+            } else if (om2 > 0.0 && rp2 > 0.0 && (rho_new.x != 0.0 || rho_new.y != 0.0)) {
+                const double2 q1 = make_double2((rho_new.x * sc.rho_prev.x + rho_new.y * sc.rho_prev.y) / rp2,
+                                                (rho_new.y * sc.rho_prev.x - rho_new.x * sc.rho_prev.y) / rp2);
+                const double2 q2 = make_double2((sc.alpha.x * sc.omega.x + sc.alpha.y * sc.omega.y) / om2,
+                                                (sc.alpha.y * sc.omega.x - sc.alpha.x * sc.omega.y) / om2);
+                sc.beta = make_double2(q1.x * q2.x - q1.y * q2.y, q1.x * q2.y + q1.y * q2.x);
+                sc.rho = rho_new;
+            } else {
+                sc.flag = 2;
+            }
+            if (sc.flag != 0) {
+                sc.alpha = sc.beta = sc.omega = zero;
+                sc.frozen = 1;
+            }
+        }
+        break;
+    }
+    default: break;
+    }
+}
+
+// Partials [base, base + 512) of a row of n, 8 per lane in a fixed pairwise
+// order (the sum over the lanes is left to wave_sum).
+__device__ __forceinline__ double block512(const double *row, int base, int n, int lane)
+{
+    double x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int i = base + 64 * k + lane;
+        x[k] = row[i < n ? i : base];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (base + 64 * k + lane >= n)
+            x[k] = 0.0;
+#pragma unroll
+    for (int w = 4; w > 0; w >>= 1)
+#pragma unroll
+        for (int k = 0; k < w; ++k)
+            x[k] += x[k + w];
+    return x[0];
+}
+
+// The scalar step that a fused update does first.  Every workgroup sums the
+// rows itself, one row per wavefront at a time, in the finalize's order (rows
+// of at most FUSED_ROW partials are one slice there: the same bits), and
+// advances the column's scalars in registers; the first workgroup stores them
+// to the other of two buffers, which the kernels after it read.  Why: on
+// small lattices an iteration is bound by the latency of its launches, and a
+// finalize is one of its own (3 us of 40).  FP64 BiCGStab on 8^3 x 16: 3.77 ms
+// with finalizes, 3.34 ms so; 4^3 x 8 3.13 and 2.62 ms; even-odd 8^3 x 16 2.53
+// and 2.28 ms.  From about 100 workgroups on the repeated sums cost more than
+// the launch (16^4 FP32, 256 workgroups: 6.9 and 7.8 ms), hence FUSED_BLOCKS.
+__host__ __device__ constexpr int fused_rows(int op) { return op == B_BI_XRP ? 8 : op == B_BI_S ? 3 : op == B_CG_P ? 2 : 1; }
+template <int OP>
+__device__ __forceinline__ Scalars fused_step(const BlasParams &p)
+{
+    constexpr int NR = fused_rows(OP);
+    __shared__ double sums[NR];
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+    Scalars sc = p.sc[0];
+    if (!sc.frozen) {  // uniform
+        for (int row = wave; row < NR; row += nw) {
+            // B_BI_S: rows 0, 1 of A, then C; B_CG_P: A (|r|^2), then C (|z|^2)
+            const bool c = (OP == B_BI_S && row == 2) || (OP == B_CG_P && row == 1);
+            const double *q = c ? p.C : p.A + (size_t)row * p.nA;
+            const double v = wave_sum(block512(q, 0, c ? p.nC : p.nA, lane));
+            if (lane == 0)
+                sums[row] = v;
+        }
+        __syncthreads();
+        if constexpr (OP == B_BI_S) {
+            if (p.iter >= 0)
+                scalar_step(F_BI_CONV, sc, sums + 2, nullptr, nullptr, 1, p.iter, 0.0);
+        } else if constexpr (OP == B_BI_XRP) {
+            scalar_step(F_BI_OMEGA_RHO, sc, sums, nullptr, nullptr, 1, p.iter, 0.0);
+        } else if constexpr (OP == B_CG_XR) {
+            scalar_step(F_CG_ALPHA, sc, sums, nullptr, nullptr, 1, p.iter, 0.0);
+        } else {
+            scalar_step(F_CG_BETA, sc, sums, sums + 1, nullptr, 1, p.iter, 0.0);
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0 && p.hflag && p.iter >= 0) {
+            p.hrr[0] = sc.rr;
+            p.hflag[0] = sc.flag;
+            p.hsc[0] = sc;
+        }
+        if constexpr (OP == B_BI_S)
+            if (!sc.frozen)
+                scalar_step(F_BI_ALPHA, sc, sums, nullptr, nullptr, 1, p.iter, 0.0);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        p.sc_out[0] = sc;
+    return sc;
+}
+
+template <int P, int OP, bool FUSE = false>
 __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
 {
     using T = typename Traits<P>::real;
@@ -92,15 +488,55 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
     const void *const A1 = p.a1 ? (const char *)p.a1 + off : nullptr;
     const void *const A2 = p.a2 ? (const char *)p.a2 + off : nullptr;
     const void *const A3 = p.a3 ? (const char *)p.a3 + off : nullptr;
-    if (p.skip_frozen && p.sc[col].frozen)  // whole workgroup
+    // a fused update has its operands under way while it does the scalar step
+    constexpr int NPRE = !FUSE ? 1 : OP == B_BI_XRP ? 5 : OP == B_CG_XR ? 4 : 2;
+    cx<T> pre[NPRE][12];
+    Scalars sc;
+    if constexpr (FUSE) {
+        const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+        if (s < V) {
+            if constexpr (OP == B_BI_S) {
+                load_site<P>(A0, V, nr, s, r, pre[0]);
+                load_site<P>(A1, V, nr, s, r, pre[1]);
+            } else if constexpr (OP == B_BI_XRP) {
+                load_site<P>(Y0, V, nr, s, r, pre[0]);
+                load_site<P>(Y2, V, nr, s, r, pre[1]);
+                load_site<P>(A1, V, nr, s, r, pre[2]);
+                load_site<P>(A2, V, nr, s, r, pre[3]);
+                load_site<P>(A3, V, nr, s, r, pre[4]);
+            } else if constexpr (OP == B_CG_XR) {
+                load_site<P>(Y0, V, nr, s, r, pre[0]);
+                load_site<P>(Y1, V, nr, s, r, pre[1]);
+                load_site<P>(A0, V, nr, s, r, pre[2]);
+                load_site<P>(A1, V, nr, s, r, pre[3]);
+            } else {
+                load_site<P>(Y0, V, nr, s, r, pre[0]);
+                load_site<P>(A0, V, nr, s, r, pre[1]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        sc = fused_step<OP>(p);
+    } else {
+        sc = p.sc[col];
+    }
+    // operand k of the op, at f
+    auto operand = [&](int k, const void *f, uint32_t s, cx<T>(&v)[12]) {
+        if constexpr (FUSE) {
+#pragma unroll
+            for (int i = 0; i < 12; ++i)
+                v[i] = pre[k][i];
+        } else {
+            load_site<P>(f, V, nr, s, r, v);
+        }
+    };
+    if (p.skip_frozen && sc.frozen)  // whole workgroup
         return;
-    if (OP == B_CG_RESTART && !p.sc[col].restart)
+    if (OP == B_CG_RESTART && !sc.restart)
         return;
     double red[NA] = {};
     for (int j = 0; j < blas_spt(OP); ++j) {
     const uint32_t s = (blockIdx.x * blas_spt(OP) + j) * blockDim.x + threadIdx.x;
     if (s < V) {
-        const Scalars &sc = p.sc[col];
         if constexpr (OP == B_RES) {  // r = b - w
             cx<T> b[12], w[12], o[12];
             load_site<P>(A0, V, nr, s, r, b);
@@ -114,10 +550,10 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
         } else if constexpr (OP == B_CG_XR) {  // x += a p ; r -= a w
             const T a = (T)sc.alpha.x;
             cx<T> x[12], rr[12], pp[12], w[12];
-            load_site<P>(Y0, V, nr, s, r, x);
-            load_site<P>(Y1, V, nr, s, r, rr);
-            load_site<P>(A0, V, nr, s, r, pp);
-            load_site<P>(A1, V, nr, s, r, w);
+            operand(0, Y0, s, x);
+            operand(1, Y1, s, rr);
+            operand(2, A0, s, pp);
+            operand(3, A1, s, w);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 x[k] = rfma(a, pp[k], x[k]);
@@ -130,8 +566,8 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
         } else if constexpr (OP == B_CG_P) {  // p = z + beta p
             const T b = (T)sc.beta.x;
             cx<T> pp[12], z[12];
-            load_site<P>(Y0, V, nr, s, r, pp);
-            load_site<P>(A0, V, nr, s, r, z);
+            operand(0, Y0, s, pp);
+            operand(1, A0, s, z);
 #pragma unroll
             for (int k = 0; k < 12; ++k)
                 pp[k] = rfma(b, pp[k], z[k]);
@@ -151,8 +587,8 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
         } else if constexpr (OP == B_BI_S) {  // s = r - alpha v (|s|^2 comes with t = D s)
             const cx<T> a{(T)sc.alpha.x, (T)sc.alpha.y};
             cx<T> rr[12], v[12];
-            load_site<P>(A0, V, nr, s, r, rr);
-            load_site<P>(A1, V, nr, s, r, v);
+            operand(0, A0, s, rr);
+            operand(1, A1, s, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k)
                 rr[k] = cfma(cx<T>{-a.re, -a.im}, v[k], rr[k]);
@@ -264,10 +700,10 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             const cx<T> a{(T)sc.alpha.x, (T)sc.alpha.y}, om{(T)sc.omega.x, (T)sc.omega.y};
             const cx<T> b{(T)sc.beta.x, (T)sc.beta.y};
             cx<T> x[12], pp[12], ss[12], t[12];
-            load_site<P>(Y0, V, nr, s, r, x);
-            load_site<P>(Y2, V, nr, s, r, pp);
-            load_site<P>(A1, V, nr, s, r, ss);
-            load_site<P>(A2, V, nr, s, r, t);
+            operand(0, Y0, s, x);
+            operand(1, Y2, s, pp);
+            operand(2, A1, s, ss);
+            operand(3, A2, s, t);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 x[k] = cfma(a, pp[k], x[k]);
@@ -279,7 +715,7 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             store_site<P>(Y1, V, nr, s, r, ss);
             red[0] += n2(ss);
             cx<T> v[12];
-            load_site<P>(A3, V, nr, s, r, v);
+            operand(4, A3, s, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 const cx<T> d = cfma(cx<T>{-om.re, -om.im}, v[k], pp[k]);
@@ -361,6 +797,19 @@ static hipError_t launch_blas_p(int op, const BlasParams &p, dim3 g, dim3 b, hip
     return hipGetLastError();
 }
 
+template <int P>
+static hipError_t launch_fused_p(int op, const BlasParams &p, dim3 g, dim3 b, hipStream_t st)
+{
+    switch (op) {
+    case B_BI_S: hipLaunchKernelGGL((blas_kernel<P, B_BI_S, true>), g, b, 0, st, p); break;
+    case B_BI_XRP: hipLaunchKernelGGL((blas_kernel<P, B_BI_XRP, true>), g, b, 0, st, p); break;
+    case B_CG_XR: hipLaunchKernelGGL((blas_kernel<P, B_CG_XR, true>), g, b, 0, st, p); break;
+    case B_CG_P: hipLaunchKernelGGL((blas_kernel<P, B_CG_P, true>), g, b, 0, st, p); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 // One workgroup per `block` sites and column.  (A grid-stride variant capped
 // at 2048 workgroups, which shrinks the finalize's input, measured slower
 // overall: the streaming kernels lost more than the finalize gained.)
@@ -380,6 +829,23 @@ hipError_t launch_blas(int prec, int op, const BlasParams &p0, int block, hipStr
     case F32: return launch_blas_p<F32>(op, p, g, b, st);
     case BF16S: return launch_blas_p<BF16S>(op, p, g, b, st);
     case F16S: return launch_blas_p<F16S>(op, p, g, b, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_blas_fused(int prec, int op, const BlasParams &p0, int block, hipStream_t st)
+{
+    BlasParams p = p0;
+    if (p.nrhs != 1 || p.seg || !p.sc_out || p.sc_out == p.sc || p.nA < 1 || p.nA > FUSED_ROW || !p.A ||
+        ((op == B_BI_S || op == B_CG_P) && (!p.C || p.nC < 1 || p.nC > FUSED_ROW)))
+        return hipErrorInvalidValue;
+    p.nblk = blas_partials(p.V, op, block);
+    dim3 g(p.nblk), b(block);
+    switch (prec) {
+    case F64: return launch_fused_p<F64>(op, p, g, b, st);
+    case F32: return launch_fused_p<F32>(op, p, g, b, st);
+    case BF16S: return launch_fused_p<BF16S>(op, p, g, b, st);
+    case F16S: return launch_fused_p<F16S>(op, p, g, b, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -438,17 +904,6 @@ constexpr int FIN_BLOCK = 512;   // partials a wavefront loads at once
 constexpr int FIN_MAX = RED_NVAL_MAX * 64;  // values x right-hand sides per partial set
 __host__ __device__ inline int fin_slices(int n) { return n > 16 * FIN_BLOCK ? 16 : n > 0 ? (n + FIN_BLOCK - 1) / FIN_BLOCK : 1; }
 
-__device__ __forceinline__ bool finite2(double a) { return isfinite(a); }
-__device__ __forceinline__ double2 cmul(double2 a, double2 b)
-{
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ double2 cdiv(double2 a, double2 b)  // b != 0
-{
-    const double d = b.x * b.x + b.y * b.y;
-    return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
-}
-
 struct RowRef {
     const double *p;
     int n;
@@ -485,23 +940,7 @@ __global__ __launch_bounds__(64 * FIN_WAVES) void finalize_kernel(FinParams p, i
             const int j = task % smax, ns = fin_slices(row.n);
             double v = 0.0;
             for (int base = j * FIN_BLOCK; j < ns && base < row.n; base += ns * FIN_BLOCK) {
-                double x[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int i = base + 64 * k + lane;
-                    x[k] = row.p[i < row.n ? i : base];
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (base + 64 * k + lane >= row.n)
-                        x[k] = 0.0;
-                // fixed pairwise order within a block of partials
-#pragma unroll
-                for (int w = 4; w > 0; w >>= 1)
-#pragma unroll
-                    for (int k = 0; k < w; ++k)
-                        x[k] += x[k + w];
-                v += x[0];
+                v += block512(row.p, base, row.n, lane);
             }
             v = wave_sum(v);
             if (lane == 0)
@@ -542,310 +981,8 @@ __global__ __launch_bounds__(64 * FIN_WAVES) void finalize_kernel(FinParams p, i
         return;
     }
     Scalars sc = p.sc[r];
-    const double2 zero = make_double2(0.0, 0.0), one = make_double2(1.0, 0.0);
-    switch (op) {
-    case F_INIT_CG: {
-        sc.rr = sA[r];
-        sc.zz = p.nvalB > 0 ? sB[r] : 0.0;  // the single-reduction form computes z in its loop
-        sc.bb = sC[r];
-        sc.rr_upd = sc.rr;
-        sc.restart = 0;
-        sc.tol2 = p.tol2v ? p.tol2v[r] : p.tol2;
-        sc.alpha = sc.beta = zero;
-        sc.flag = 0;
-        sc.conv_iter = 0;
-        if (!finite2(sc.rr) || !finite2(sc.zz) || !finite2(sc.bb))
-            sc.flag = 3;
-        else if (sc.rr <= sc.tol2 * sc.bb)
-            sc.flag = 1;
-        sc.frozen = sc.flag != 0;
-        break;
-    }
-    case F_CG_ALPHA: {
-        const double ww = sA[r];
-        if (sc.flag == 0) {
-            if (!finite2(ww))
-                sc.flag = 3;
-            else if (ww > 0.0) {
-                sc.alpha = make_double2(sc.zz / ww, 0.0);
-                break;
-            } else
-                sc.flag = 2;
-        }
-        sc.alpha = zero;
-        break;
-    }
-    case F_CG_BETA: {
-        const double rr = sA[r], zz = sB[r];
-        if (sc.flag == 0) {
-            sc.rr = rr;
-            if (!finite2(rr) || !finite2(zz))
-                sc.flag = 3;
-            else if (rr <= sc.tol2 * sc.bb) {
-                sc.flag = 1;
-                sc.conv_iter = p.iter + 1;
-            } else if (sc.zz > 0.0) {
-                sc.beta = make_double2(zz / sc.zz, 0.0);
-                sc.zz = zz;
-                break;
-            } else
-                sc.flag = 2;
-        }
-        sc.beta = zero;
-        sc.frozen = 1;  // end of the iteration with flag != 0
-        break;
-    }
-    case F_CG_RELIABLE: {
-        // r was replaced by the (converted) true residual and z = D^dag r
-        // recomputed; the search direction is kept
-        if (sc.flag == 0) {
-            const double rr = sA[r], zz = sB[r];
-            sc.rr = rr;
-            if (!finite2(rr) || !finite2(zz))
-                sc.flag = 3;
-            else if (rr <= sc.tol2 * sc.bb) {
-                sc.flag = 1;
-                sc.conv_iter = p.iter + 1;
-            } else if (zz > 0.0) {
-                sc.zz = zz;
-                // |r| has grown since the previous update: the low-precision
-                // recurrence has lost its search space; start it again from z
-                sc.restart = rr > sc.rr_upd;
-                sc.rr_upd = rr;
-            } else
-                sc.flag = 2;
-            if (sc.flag != 0) {
-                sc.alpha = sc.beta = zero;
-                sc.frozen = 1;
-            }
-        }
-        break;
-    }
-    case F_INIT_BI: {
-        sc.rr = sA[r];
-        sc.bb = sC[r];
-        sc.tol2 = p.tol2v ? p.tol2v[r] : p.tol2;
-        sc.rho = make_double2(sc.rr, 0.0);
-        sc.rho_prev = sc.rho;  // <rh, r0> with rh = r0
-        sc.alpha = sc.omega = one;
-        sc.beta = zero;  // p = v = 0 -> first p = r
-        sc.brk = 0;
-        sc.flag = 0;
-        sc.conv_iter = 0;
-        if (!finite2(sc.rr) || !finite2(sc.bb))
-            sc.flag = 3;
-        else if (sc.rr <= sc.tol2 * sc.bb)
-            sc.flag = 1;
-        sc.frozen = sc.flag != 0;
-        break;
-    }
-    case F_BI_ALPHA: {
-        const double2 rv = make_double2(sA[r], sA[nr + r]);
-        if (sc.flag == 0) {
-            const double d = rv.x * rv.x + rv.y * rv.y;
-            if (!finite2(d))
-                sc.flag = 3;
-            else if (d > 0.0) {  // alpha = rho / <rh, v>
-                sc.alpha = make_double2((sc.rho.x * rv.x + sc.rho.y * rv.y) / d, (sc.rho.y * rv.x - sc.rho.x * rv.y) / d);
-                break;
-            } else
-                sc.flag = 2;
-        }
-        sc.alpha = zero;
-        break;
-    }
-    case F_BI_OMEGA_RHO: {
-        // omega = <t, s> / <t, t> (or stop: converged on |s|, t = 0, NaN);
-        // then, with r' = s - omega t still to be formed,
-        // rho' = <rh, r'> = <rh, s> - omega <rh, t> and beta = (rho'/rho)(alpha/omega)
-        const double ss = sA[7 * nr + r];
-        const double st_re = sA[r], st_im = sA[nr + r], tt = sA[2 * nr + r];
-        const double2 hs = make_double2(sA[3 * nr + r], sA[4 * nr + r]);
-        const double2 ht = make_double2(sA[5 * nr + r], sA[6 * nr + r]);
-        sc.ss = ss;
-        sc.brk = 0;
-        sc.beta = zero;
-        if (sc.flag == 0) {
-            if (!finite2(ss) || !finite2(tt) || !finite2(st_re) || !finite2(st_im))
-                sc.flag = 3;
-            else if (ss <= sc.tol2 * sc.bb) {  // x += alpha p ; r = s  (omega = 0)
-                sc.flag = 1;
-                sc.conv_iter = p.iter + 1;
-            } else if (tt > 0.0) {
-                const double2 om = make_double2(st_re / tt, -st_im / tt);
-                sc.omega = om;
-                const double2 rho_new = make_double2(hs.x - (om.x * ht.x - om.y * ht.y), hs.y - (om.x * ht.y + om.y * ht.x));
-                const double om2 = om.x * om.x + om.y * om.y;
-                const double rho2 = sc.rho.x * sc.rho.x + sc.rho.y * sc.rho.y;
-                if (!finite2(rho_new.x) || !finite2(rho_new.y))
-                    sc.brk = 2;
-                else if (om2 > 0.0 && rho2 > 0.0 && (rho_new.x != 0.0 || rho_new.y != 0.0)) {
-                    const double2 q1 = make_double2((rho_new.x * sc.rho.x + rho_new.y * sc.rho.y) / rho2,
-                                                    (rho_new.y * sc.rho.x - rho_new.x * sc.rho.y) / rho2);
-                    const double2 q2 = make_double2((sc.alpha.x * om.x + sc.alpha.y * om.y) / om2,
-                                                    (sc.alpha.y * om.x - sc.alpha.x * om.y) / om2);
-                    sc.beta = make_double2(q1.x * q2.x - q1.y * q2.y, q1.x * q2.y + q1.y * q2.x);
-                    sc.rho_prev = sc.rho;
-                    sc.rho = rho_new;
-                } else
-                    sc.brk = 1;
-                break;
-            } else
-                sc.flag = 2;
-        } else
-            sc.alpha = zero;
-        sc.omega = zero;
-        break;
-    }
-    case F_BI_CONV: {
-        const double rr = sA[r];
-        if (sc.flag == 0) {
-            sc.rr = rr;
-            if (!finite2(rr) || sc.brk == 2)
-                sc.flag = 3;
-            else if (rr <= sc.tol2 * sc.bb) {
-                sc.flag = 1;
-                sc.conv_iter = p.iter + 1;
-            } else if (sc.brk == 1)
-                sc.flag = 2;
-            else
-                break;
-        } else if (sc.flag == 1 && sc.conv_iter == p.iter + 1) {
-            sc.rr = rr;  // converged on |s| this iteration: r = s
-        }
-        sc.beta = zero;
-        sc.alpha = zero;
-        sc.omega = zero;
-        sc.frozen = 1;  // end of the iteration with flag != 0
-        break;
-    }
-    case F_CG1: {
-        // CG on the normal equations with one reduction phase per iteration
-        // (Chronopoulos and Gear's form): gamma = |z|^2 with z = D^dag r,
-        // delta = |D z|^2; beta = gamma / gamma_prev and
-        // alpha = gamma / (delta - beta gamma / alpha_prev), where the
-        // denominator equals |D p|^2 for p = z + beta p_prev
-        const double rr = p.nvalC > 0 ? sC[r] : sc.rr, gam = sA[r], del = sB[r];
-        if (sc.flag == 0) {
-            sc.rr = rr;
-            if (!finite2(rr) || !finite2(gam) || !finite2(del))
-                sc.flag = 3;
-            else if (rr <= sc.tol2 * sc.bb) {
-                sc.flag = 1;
-                sc.conv_iter = p.iter;
-            } else {
-                const double beta = p.iter > 0 && sc.zz > 0.0 ? gam / sc.zz : 0.0;
-                const double den = beta != 0.0 ? del - beta * gam / sc.alpha.x : del;
-                if (gam > 0.0 && den > 0.0 && finite2(den)) {
-                    sc.alpha = make_double2(gam / den, 0.0);
-                    sc.beta = make_double2(beta, 0.0);
-                    sc.zz = gam;
-                    break;
-                }
-                sc.flag = 2;
-            }
-        }
-        sc.alpha = sc.beta = zero;
-        sc.frozen = 1;  // the update pass of this iteration is skipped
-        break;
-    }
-    case F_SR: {
-        // BiCGStab with one reduction phase per iteration.  With u = D r,
-        // v = D p and q = D v known, s = r - alpha v and t = D s = u - alpha q
-        // never need to be formed before the scalars:
-        //   <t, s> = <u, r> - alpha <u, v> - conj(alpha) <q, r> + |alpha|^2 <q, v>
-        //   <t, t> = |u|^2 - 2 Re(alpha <u, q>) + |alpha|^2 |q|^2
-        //   rho'   = <rh, s> - omega <rh, t>
-        //          = rho - alpha <rh, v> - omega (<rh, u> - alpha <rh, q>)
-        const double rr = p.nvalC > 0 ? sC[r] : sc.rr;
-        const double2 hv = make_double2(sA[r], sA[nr + r]), hu = make_double2(sA[2 * nr + r], sA[3 * nr + r]);
-        const double2 ur = make_double2(sA[4 * nr + r], sA[5 * nr + r]), uv = make_double2(sA[6 * nr + r], sA[7 * nr + r]);
-        const double uu = sA[8 * nr + r];
-        const double2 vq = make_double2(sB[r], sB[nr + r]);
-        const double qq = sB[2 * nr + r];
-        const double2 hq = make_double2(sB[3 * nr + r], sB[4 * nr + r]), rq = make_double2(sB[5 * nr + r], sB[6 * nr + r]);
-        const double2 uq = make_double2(sB[7 * nr + r], sB[8 * nr + r]);
-        if (sc.flag == 0) {
-            sc.rr = rr;
-            const double d = hv.x * hv.x + hv.y * hv.y;
-            if (!finite2(rr) || !finite2(d) || !finite2(uu) || !finite2(qq) || sc.brk == 2)
-                sc.flag = 3;
-            else if (rr <= sc.tol2 * sc.bb) {
-                sc.flag = 1;
-                sc.conv_iter = p.iter;
-            } else if (sc.brk == 1 || !(d > 0.0))
-                sc.flag = 2;
-            if (sc.flag == 0) {
-                const double2 a = cdiv(sc.rho, hv);
-                const double a2 = a.x * a.x + a.y * a.y;
-                // <t, s>
-                const double2 auv = cmul(a, uv);
-                const double2 aqr = cmul(make_double2(a.x, -a.y), make_double2(rq.x, -rq.y));
-                const double2 ts = make_double2(ur.x - auv.x - aqr.x + a2 * vq.x, ur.y - auv.y - aqr.y - a2 * vq.y);
-                const double tt = uu - 2.0 * cmul(a, uq).x + a2 * qq;
-                sc.brk = 0;
-                if (!finite2(ts.x) || !finite2(ts.y) || !finite2(tt)) {
-                    sc.flag = 3;
-                } else if (!(tt > 0.0)) {
-                    sc.flag = 2;
-                } else {
-                    const double2 om = make_double2(ts.x / tt, ts.y / tt);
-                    const double2 ahq = cmul(a, hq);
-                    const double2 w1 = cmul(om, make_double2(hu.x - ahq.x, hu.y - ahq.y));
-                    const double2 ahv = cmul(a, hv);
-                    const double2 rho_new = make_double2(sc.rho.x - ahv.x - w1.x, sc.rho.y - ahv.y - w1.y);
-                    sc.alpha = a;
-                    sc.omega = om;
-                    sc.beta = zero;
-                    if (!finite2(rho_new.x) || !finite2(rho_new.y))
-                        sc.brk = 2;
-                    else if ((om.x != 0.0 || om.y != 0.0) && (rho_new.x != 0.0 || rho_new.y != 0.0))
-                        sc.beta = cmul(cdiv(rho_new, sc.rho), cdiv(a, om));
-                    else
-                        sc.brk = 1;  // this step is taken; the next check reports the breakdown
-                    sc.rho_prev = sc.rho;
-                    sc.rho = rho_new;
-                    break;
-                }
-            }
-        }
-        sc.alpha = sc.beta = sc.omega = zero;
-        sc.frozen = 1;
-        break;
-    }
-    case F_BI_RELIABLE: {
-        // r was just replaced by the (converted) true residual; recompute
-        // rho = <rh, r> and beta = (rho / rho_prev)(alpha / omega) from it
-        if (sc.flag == 0) {
-            const double rr = sA[2 * nr + r];
-            const double2 rho_new = make_double2(sA[r], sA[nr + r]);
-            const double om2 = sc.omega.x * sc.omega.x + sc.omega.y * sc.omega.y;
-            const double rp2 = sc.rho_prev.x * sc.rho_prev.x + sc.rho_prev.y * sc.rho_prev.y;
-            sc.rr = rr;
-            if (!finite2(rr) || !finite2(rho_new.x) || !finite2(rho_new.y)) {
-                sc.flag = 3;
-            } else if (rr <= sc.tol2 * sc.bb) {
-                sc.flag = 1;
-                sc.conv_iter = p.iter + 1;
-            } else if (om2 > 0.0 && rp2 > 0.0 && (rho_new.x != 0.0 || rho_new.y != 0.0)) {
-                const double2 q1 = make_double2((rho_new.x * sc.rho_prev.x + rho_new.y * sc.rho_prev.y) / rp2,
-                                                (rho_new.y * sc.rho_prev.x - rho_new.x * sc.rho_prev.y) / rp2);
-                const double2 q2 = make_double2((sc.alpha.x * sc.omega.x + sc.alpha.y * sc.omega.y) / om2,
-                                                (sc.alpha.y * sc.omega.x - sc.alpha.x * sc.omega.y) / om2);
-                sc.beta = make_double2(q1.x * q2.x - q1.y * q2.y, q1.x * q2.y + q1.y * q2.x);
-                sc.rho = rho_new;
-            } else {
-                sc.flag = 2;
-            }
-            if (sc.flag != 0) {
-                sc.alpha = sc.beta = sc.omega = zero;
-                sc.frozen = 1;
-            }
-        }
-        break;
-    }
-    default: break;
-    }
+    scalar_step(op, sc, sA + r, p.nvalB > 0 ? sB + r : nullptr, p.nvalC > 0 ? sC + r : nullptr, nr, p.iter,
+                p.tol2v ? p.tol2v[r] : p.tol2);
     p.sc[r] = sc;
     if (p.hflag) {  // mirror the status into host-visible memory for polling
         p.hrr[r] = sc.rr;

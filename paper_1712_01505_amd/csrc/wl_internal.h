@@ -264,8 +264,25 @@ struct BlasParams {
     int nrhs;
     int nblk;
     int skip_frozen;   // in a solver loop: skip frozen columns
+    // fused scalar step (blas_fused_ok): the kernel sums the rows of A (the
+    // step's values) and, where it closes an iteration, of C itself, advances
+    // *sc into *sc_out and mirrors the status of iteration `iter` (negative:
+    // no iteration to close)
+    const double *A, *C;
+    int nA, nC;        // partials per row
+    Scalars *sc_out;
+    int iter;
+    int *hflag;
+    double *hrr;
+    Scalars *hsc;
 };
 hipError_t launch_blas(int prec, int op, const BlasParams &p, int block, hipStream_t st);
+// The update `op` with the scalar step in front of it done by itself (one
+// column): B_BI_S (F_BI_CONV of the iteration before, F_BI_ALPHA), B_BI_XRP
+// (F_BI_OMEGA_RHO), B_CG_XR (F_CG_ALPHA), B_CG_P (F_CG_BETA).
+hipError_t launch_blas_fused(int prec, int op, const BlasParams &p, int block, hipStream_t st);
+constexpr int FUSED_ROW = 512;   // longest row of partials a fused step can sum (one slice of the finalize)
+constexpr int FUSED_BLOCKS = 64; // workgroups of an update that does its own scalar step (see blas_kernel)
 int blas_partials(uint32_t V, int op, int block);  // workgroups (= partial sums per RHS) of one launch
 int blas_nval(int op);
 int blas_sites_per_thread(int op);

@@ -215,6 +215,7 @@ struct Engine {
     double *part[3];
     int nblk[3] = {0, 0, 0}, nval[3] = {0, 0, 0};
     Scalars *sc;
+    Scalars *sc_alt = nullptr;  // second buffer of the fused scalar steps (init: in part[2])
     double *sums;
     Scalars *sc_host;  // pinned
     HostBufs *hb;
@@ -401,6 +402,10 @@ struct Engine {
             return WL_EWORKSPACE;
         if (!(sums = (double *)a.take(sizeof(double) * 3 * nrhs)))
             return WL_EWORKSPACE;
+        // set 2 holds one row at a time in form 0: its rows 4..8 (at least 11
+        // partials of a column each) have room for a second set of scalars
+        static_assert(5 * 11 * sizeof(double) >= sizeof(Scalars) && RED_NVAL_MAX >= 9, "");
+        sc_alt = (Scalars *)(part[2] + 4 * (size_t)nrhs * max_nblk(V, o->g.dims[3]));
         return WL_OK;
     }
 
@@ -497,6 +502,68 @@ struct Engine {
         }
         ++kernels;
         WL_TRY(launch_blas(prec, bop, p, BLAS_BLOCK, st));
+        return WL_OK;
+    }
+
+    // Small lattices with one column: the updates do the scalar steps in front
+    // of them (launch_blas_fused) and no finalize is launched inside the loop.
+    // Only where every row of partials is at most FUSED_ROW long, and not
+    // under reliable updates, which read and replace the scalars in between.
+    bool fused(bool bicg) const
+    {
+        if (!lats.empty() || nrhs != 1 || group != 1 || form != 0 || on_iter || rel_decide)
+            return false;
+        if (blas_partials(V, B_NORM, BLAS_BLOCK) > FUSED_BLOCKS)
+            return false;
+        const int reds[2] = {bicg ? (int)RED_DOTV : (int)RED_NORM, bicg ? (int)RED_BICG : (int)RED_NORM};
+        for (int k = 0; k < 2; ++k) {
+            const int dag = (bicg ? 0 : k) ^ adj;
+            const int n = eo ? eo_partials(V, nrhs) : stencil_partials(launch_for(op, nrhs, reds[k], dag), op->g.dims, V, nrhs);
+            if (n > FUSED_ROW)
+                return false;
+        }
+        return true;
+    }
+
+    // The fused update: rows of set a (and c), scalars from sc into the other
+    // buffer, which becomes sc.  close: the iteration whose status the step
+    // decides and mirrors (negative: none).
+    int blas_step(int bop, void *y0, void *y1, const void *a0, const void *a1, const void *a2, const void *a3, void *y2,
+                  int a, int c, int out, int close)
+    {
+        BlasParams p{};
+        p.skip_frozen = 1;
+        p.y0 = y0;
+        p.y1 = y1;
+        p.y2 = y2;
+        p.a0 = a0;
+        p.a1 = a1;
+        p.a2 = a2;
+        p.a3 = a3;
+        p.sc = sc;
+        p.sc_out = sc_alt;
+        p.A = part[a];
+        p.nA = nblk[a];
+        if (c >= 0) {
+            p.C = part[c];
+            p.nC = nblk[c];
+        }
+        p.iter = close;
+        const bool ends = bop == B_BI_S || bop == B_CG_P;
+        p.hflag = ends ? hb->dflag : nullptr;
+        p.hrr = ends ? hb->drr : nullptr;
+        p.hsc = ends ? hb->dsc : nullptr;
+        p.partials = out >= 0 ? part[out] : nullptr;
+        p.V = V;
+        p.nrhs = nrhs;
+        if (out >= 0) {
+            nblk[out] = blas_partials(V, bop, BLAS_BLOCK);
+            nval[out] = blas_nval(bop);
+            lenp[out] = nullptr;
+        }
+        ++kernels;
+        WL_TRY(launch_blas_fused(prec, bop, p, BLAS_BLOCK, st));
+        std::swap(sc, sc_alt);
         return WL_OK;
     }
 
@@ -683,6 +750,20 @@ struct Engine {
                 return rc;
             WL_TRY(hipStreamSynchronize(st));
             bool stop = host_all_done();
+            const bool one = fused(false);
+            while (one && !stop && it < maxiter) {
+                if ((rc = stencil(w, p, 0, RED_NORM, nullptr, 0, true)))
+                    return rc;
+                if ((rc = blas_step(B_CG_XR, x, r, p, w, nullptr, nullptr, nullptr, 0, -1, 2, it)))
+                    return rc;
+                if ((rc = stencil(z, r, 1, RED_NORM, nullptr, 1, true)))
+                    return rc;
+                if ((rc = blas_step(B_CG_P, p, nullptr, z, nullptr, nullptr, nullptr, nullptr, 2, 1, -1, it)))
+                    return rc;
+                if ((rc = mark(it, &stop)))
+                    return rc;
+                ++it;
+            }
             while (!stop && it < maxiter) {
                 if ((rc = stencil(w, p, 0, RED_NORM, nullptr, 0, true)))
                     return rc;
@@ -724,6 +805,27 @@ struct Engine {
                 return rc;
             WL_TRY(hipStreamSynchronize(st));
             bool stop = host_all_done();
+            if (fused(true)) {
+                // the check that closes an iteration is done by the next one's
+                // first update (the product before it only fills v then)
+                while (!stop && it < maxiter) {
+                    if ((rc = stencil(vv, p, 0, RED_DOTV, rh, 0, true)))
+                        return rc;
+                    if (it == 0)
+                        nblk[2] = 1;  // nothing to close yet: row C is not used
+                    if ((rc = blas_step(B_BI_S, s, nullptr, r, vv, nullptr, nullptr, nullptr, 0, 2, -1, it - 1)))
+                        return rc;
+                    if ((rc = stencil(t, s, 0, RED_BICG, rh, 1, true)))
+                        return rc;
+                    if ((rc = blas_step(B_BI_XRP, x, r, nullptr, s, t, vv, p, 1, -1, 2, it)))
+                        return rc;
+                    if ((rc = mark(it, &stop)))
+                        return rc;
+                    ++it;
+                }
+                if (it > 0 && (rc = fin(F_BI_CONV, 2, -1, -1, it - 1, tol2)))
+                    return rc;
+            }
             while (!stop && it < maxiter) {
                 if (pending_p) {  // p = r + beta (p - omega v) with the replaced r and its beta
                     if ((rc = blas(B_BI_P, p, nullptr, r, vv, nullptr, nullptr, -1, true)))
