@@ -58,7 +58,7 @@ __device__ __forceinline__ void round_if_scaled(cx<typename Traits<P>::real> (&v
 // partial sums)
 __host__ __device__ constexpr int blas_nv(int op)
 {
-    return (op == B_RES || op == B_CG_XR || op == B_NORM || op == B_BI_XRP || op == B_CG1 || op == B_SR_XR ||
+    return (op == B_RES || op == B_CG_R || op == B_NORM || op == B_BI_XRP || op == B_CG1 || op == B_SR_XR ||
             op == B_INIT)                                                                                   ? 1
            : (op == B_BI_XR || op == B_DOT_NORM)                                                           ? 3
            : op == B_SR_PV                                                                                 ? 9
@@ -103,6 +103,8 @@ __device__ __forceinline__ void scalar_step(int op, Scalars &sc, const double *A
     }
     case F_CG_ALPHA: {
         const double ww = A[0];
+        if (sc.frozen == 2)
+            sc.frozen = 1;  // x has its last update
         if (sc.flag == 0) {
             if (!finite2(ww))
                 sc.flag = 3;
@@ -132,7 +134,8 @@ __device__ __forceinline__ void scalar_step(int op, Scalars &sc, const double *A
                 sc.flag = 2;
         }
         sc.beta = zero;
-        sc.frozen = 1;  // end of the iteration with flag != 0
+        if (!sc.frozen)
+            sc.frozen = 2;  // end of the iteration with flag != 0: x += alpha p is still due
         break;
     }
     case F_CG_RELIABLE: {
@@ -420,7 +423,7 @@ __device__ __forceinline__ double block512(const double *row, int base, int n, i
 // with finalizes, 3.34 ms so; 4^3 x 8 3.13 and 2.62 ms; even-odd 8^3 x 16 2.53
 // and 2.28 ms.  From about 100 workgroups on the repeated sums cost more than
 // the launch (16^4 FP32, 256 workgroups: 6.9 and 7.8 ms), hence FUSED_BLOCKS.
-__host__ __device__ constexpr int fused_rows(int op) { return op == B_BI_XRP ? 8 : op == B_BI_S ? 3 : op == B_CG_P ? 2 : 1; }
+__host__ __device__ constexpr int fused_rows(int op) { return op == B_BI_XRP ? 8 : op == B_BI_S ? 3 : op == B_CG_XP ? 2 : 1; }
 template <int OP>
 __device__ __forceinline__ Scalars fused_step(const BlasParams &p)
 {
@@ -430,8 +433,8 @@ __device__ __forceinline__ Scalars fused_step(const BlasParams &p)
     Scalars sc = p.sc[0];
     if (!sc.frozen) {  // uniform
         for (int row = wave; row < NR; row += nw) {
-            // B_BI_S: rows 0, 1 of A, then C; B_CG_P: A (|r|^2), then C (|z|^2)
-            const bool c = (OP == B_BI_S && row == 2) || (OP == B_CG_P && row == 1);
+            // B_BI_S: rows 0, 1 of A, then C; B_CG_XP: A (|r|^2), then C (|z|^2)
+            const bool c = (OP == B_BI_S && row == 2) || (OP == B_CG_XP && row == 1);
             const double *q = c ? p.C : p.A + (size_t)row * p.nA;
             const double v = wave_sum(block512(q, 0, c ? p.nC : p.nA, lane));
             if (lane == 0)
@@ -443,7 +446,7 @@ __device__ __forceinline__ Scalars fused_step(const BlasParams &p)
                 scalar_step(F_BI_CONV, sc, sums + 2, nullptr, nullptr, 1, p.iter, 0.0);
         } else if constexpr (OP == B_BI_XRP) {
             scalar_step(F_BI_OMEGA_RHO, sc, sums, nullptr, nullptr, 1, p.iter, 0.0);
-        } else if constexpr (OP == B_CG_XR) {
+        } else if constexpr (OP == B_CG_R) {
             scalar_step(F_CG_ALPHA, sc, sums, nullptr, nullptr, 1, p.iter, 0.0);
         } else {
             scalar_step(F_CG_BETA, sc, sums, sums + 1, nullptr, 1, p.iter, 0.0);
@@ -457,6 +460,9 @@ __device__ __forceinline__ Scalars fused_step(const BlasParams &p)
             if (!sc.frozen)
                 scalar_step(F_BI_ALPHA, sc, sums, nullptr, nullptr, 1, p.iter, 0.0);
     }
+    if constexpr (OP == B_CG_R)
+        if (sc.frozen == 2)
+            sc.frozen = 1;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         p.sc_out[0] = sc;
     return sc;
@@ -489,7 +495,7 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
     const void *const A2 = p.a2 ? (const char *)p.a2 + off : nullptr;
     const void *const A3 = p.a3 ? (const char *)p.a3 + off : nullptr;
     // a fused update has its operands under way while it does the scalar step
-    constexpr int NPRE = !FUSE ? 1 : OP == B_BI_XRP ? 5 : OP == B_CG_XR ? 4 : 2;
+    constexpr int NPRE = !FUSE ? 1 : OP == B_BI_XRP ? 5 : OP == B_CG_XP ? 3 : 2;
     cx<T> pre[NPRE][12];
     Scalars sc;
     if constexpr (FUSE) {
@@ -504,14 +510,13 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
                 load_site<P>(A1, V, nr, s, r, pre[2]);
                 load_site<P>(A2, V, nr, s, r, pre[3]);
                 load_site<P>(A3, V, nr, s, r, pre[4]);
-            } else if constexpr (OP == B_CG_XR) {
-                load_site<P>(Y0, V, nr, s, r, pre[0]);
-                load_site<P>(Y1, V, nr, s, r, pre[1]);
-                load_site<P>(A0, V, nr, s, r, pre[2]);
-                load_site<P>(A1, V, nr, s, r, pre[3]);
+            } else if constexpr (OP == B_CG_R) {
+                load_site<P>(Y1, V, nr, s, r, pre[0]);
+                load_site<P>(A1, V, nr, s, r, pre[1]);
             } else {
                 load_site<P>(Y0, V, nr, s, r, pre[0]);
                 load_site<P>(A0, V, nr, s, r, pre[1]);
+                load_site<P>(Y1, V, nr, s, r, pre[2]);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -529,7 +534,7 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             load_site<P>(f, V, nr, s, r, v);
         }
     };
-    if (p.skip_frozen && sc.frozen)  // whole workgroup
+    if (p.skip_frozen && (OP == B_CG_XP ? sc.frozen == 1 : sc.frozen != 0))  // whole workgroup
         return;
     if (OP == B_CG_RESTART && !sc.restart)
         return;
@@ -547,30 +552,32 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             round_if_scaled<P>(o);
             store_site<P>(Y0, V, nr, s, r, o);
             red[0] += n2(o);
-        } else if constexpr (OP == B_CG_XR) {  // x += a p ; r -= a w
+        } else if constexpr (OP == B_CG_R) {  // r -= a w
             const T a = (T)sc.alpha.x;
-            cx<T> x[12], rr[12], pp[12], w[12];
-            operand(0, Y0, s, x);
-            operand(1, Y1, s, rr);
-            operand(2, A0, s, pp);
-            operand(3, A1, s, w);
+            cx<T> rr[12], w[12];
+            operand(0, Y1, s, rr);
+            operand(1, A1, s, w);
+#pragma unroll
+            for (int k = 0; k < 12; ++k)
+                rr[k] = rfma(-a, w[k], rr[k]);
+            round_if_scaled<P>(rr);
+            store_site<P>(Y1, V, nr, s, r, rr);
+            red[0] += n2(rr);
+        } else if constexpr (OP == B_CG_XP) {  // x += a p ; p = z + beta p
+            // x waits for the pass that reads p anyway: 8 vector streams per
+            // iteration instead of 9 (a domain-wall CG on 16^3 x 32 x 8 in FP32
+            // 193 -> 188 ms)
+            const T a = (T)sc.alpha.x, b = (T)sc.beta.x;
+            cx<T> x[12], pp[12], z[12];
+            operand(0, Y0, s, pp);
+            operand(1, A0, s, z);
+            operand(2, Y1, s, x);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 x[k] = rfma(a, pp[k], x[k]);
-                rr[k] = rfma(-a, w[k], rr[k]);
-            }
-            round_if_scaled<P>(rr);
-            store_site<P>(Y0, V, nr, s, r, x);
-            store_site<P>(Y1, V, nr, s, r, rr);
-            red[0] += n2(rr);
-        } else if constexpr (OP == B_CG_P) {  // p = z + beta p
-            const T b = (T)sc.beta.x;
-            cx<T> pp[12], z[12];
-            operand(0, Y0, s, pp);
-            operand(1, A0, s, z);
-#pragma unroll
-            for (int k = 0; k < 12; ++k)
                 pp[k] = rfma(b, pp[k], z[k]);
+            }
+            store_site<P>(Y1, V, nr, s, r, x);
             store_site<P>(Y0, V, nr, s, r, pp);
         } else if constexpr (OP == B_BI_P) {  // p = r + beta (p - omega v)
             const cx<T> b{(T)sc.beta.x, (T)sc.beta.y}, om{(T)sc.omega.x, (T)sc.omega.y};
@@ -777,8 +784,8 @@ static hipError_t launch_blas_p(int op, const BlasParams &p, dim3 g, dim3 b, hip
 {
     switch (op) {
     case B_RES: hipLaunchKernelGGL((blas_kernel<P, B_RES>), g, b, 0, st, p); break;
-    case B_CG_XR: hipLaunchKernelGGL((blas_kernel<P, B_CG_XR>), g, b, 0, st, p); break;
-    case B_CG_P: hipLaunchKernelGGL((blas_kernel<P, B_CG_P>), g, b, 0, st, p); break;
+    case B_CG_R: hipLaunchKernelGGL((blas_kernel<P, B_CG_R>), g, b, 0, st, p); break;
+    case B_CG_XP: hipLaunchKernelGGL((blas_kernel<P, B_CG_XP>), g, b, 0, st, p); break;
     case B_BI_P: hipLaunchKernelGGL((blas_kernel<P, B_BI_P>), g, b, 0, st, p); break;
     case B_BI_S: hipLaunchKernelGGL((blas_kernel<P, B_BI_S>), g, b, 0, st, p); break;
     case B_BI_XR: hipLaunchKernelGGL((blas_kernel<P, B_BI_XR>), g, b, 0, st, p); break;
@@ -803,8 +810,8 @@ static hipError_t launch_fused_p(int op, const BlasParams &p, dim3 g, dim3 b, hi
     switch (op) {
     case B_BI_S: hipLaunchKernelGGL((blas_kernel<P, B_BI_S, true>), g, b, 0, st, p); break;
     case B_BI_XRP: hipLaunchKernelGGL((blas_kernel<P, B_BI_XRP, true>), g, b, 0, st, p); break;
-    case B_CG_XR: hipLaunchKernelGGL((blas_kernel<P, B_CG_XR, true>), g, b, 0, st, p); break;
-    case B_CG_P: hipLaunchKernelGGL((blas_kernel<P, B_CG_P, true>), g, b, 0, st, p); break;
+    case B_CG_R: hipLaunchKernelGGL((blas_kernel<P, B_CG_R, true>), g, b, 0, st, p); break;
+    case B_CG_XP: hipLaunchKernelGGL((blas_kernel<P, B_CG_XP, true>), g, b, 0, st, p); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -837,7 +844,7 @@ hipError_t launch_blas_fused(int prec, int op, const BlasParams &p0, int block, 
 {
     BlasParams p = p0;
     if (p.nrhs != 1 || p.seg || !p.sc_out || p.sc_out == p.sc || p.nA < 1 || p.nA > FUSED_ROW || !p.A ||
-        ((op == B_BI_S || op == B_CG_P) && (!p.C || p.nC < 1 || p.nC > FUSED_ROW)))
+        ((op == B_BI_S || op == B_CG_XP) && (!p.C || p.nC < 1 || p.nC > FUSED_ROW)))
         return hipErrorInvalidValue;
     p.nblk = blas_partials(p.V, op, block);
     dim3 g(p.nblk), b(block);

@@ -212,14 +212,16 @@ struct Scalars {
     int flag;             // 0 running, 1 converged, 2 breakdown, 3 NaN/Inf
     int conv_iter;
     int frozen;           // set at the end of an iteration once flag != 0: loop kernels skip the column
+                          // (CGNR: 2 until the next iteration, whose first step makes it 1: the
+                          // iteration that set it still adds its alpha p to x)
     int restart;          // CGNR reliable update without progress: restart the search direction
     int brk;              // merged BiCGStab: 1 rho or omega degenerate, 2 non-finite (acted on at F_BI_CONV)
 };
 
 enum BlasOp {
     B_RES = 0,        // r = b - w                      ; |r|^2
-    B_CG_XR = 1,      // x += a p ; r -= a w            ; |r|^2
-    B_CG_P = 2,       // p = z + beta p
+    B_CG_R = 1,       // r -= a w                       ; |r|^2
+    B_CG_XP = 2,      // x += a p ; p = z + beta p
     B_BI_P = 3,       // p = r + beta (p - omega v)
     B_BI_S = 4,       // s = r - alpha v                ; |s|^2
     B_BI_XR = 5,      // x += alpha p + omega s ; r = s - omega t ; |r|^2, <rh, r>  (a3 = rh)
@@ -279,7 +281,7 @@ struct BlasParams {
 hipError_t launch_blas(int prec, int op, const BlasParams &p, int block, hipStream_t st);
 // The update `op` with the scalar step in front of it done by itself (one
 // column): B_BI_S (F_BI_CONV of the iteration before, F_BI_ALPHA), B_BI_XRP
-// (F_BI_OMEGA_RHO), B_CG_XR (F_CG_ALPHA), B_CG_P (F_CG_BETA).
+// (F_BI_OMEGA_RHO), B_CG_R (F_CG_ALPHA), B_CG_XP (F_CG_BETA).
 hipError_t launch_blas_fused(int prec, int op, const BlasParams &p, int block, hipStream_t st);
 constexpr int FUSED_ROW = 512;   // longest row of partials a fused step can sum (one slice of the finalize)
 constexpr int FUSED_BLOCKS = 64; // workgroups of an update that does its own scalar step (see blas_kernel)

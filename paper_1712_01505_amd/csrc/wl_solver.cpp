@@ -549,7 +549,7 @@ struct Engine {
             p.nC = nblk[c];
         }
         p.iter = close;
-        const bool ends = bop == B_BI_S || bop == B_CG_P;
+        const bool ends = bop == B_BI_S || bop == B_CG_XP;
         p.hflag = ends ? hb->dflag : nullptr;
         p.hrr = ends ? hb->drr : nullptr;
         p.hsc = ends ? hb->dsc : nullptr;
@@ -754,11 +754,11 @@ struct Engine {
             while (one && !stop && it < maxiter) {
                 if ((rc = stencil(w, p, 0, RED_NORM, nullptr, 0, true)))
                     return rc;
-                if ((rc = blas_step(B_CG_XR, x, r, p, w, nullptr, nullptr, nullptr, 0, -1, 2, it)))
+                if ((rc = blas_step(B_CG_R, nullptr, r, nullptr, w, nullptr, nullptr, nullptr, 0, -1, 2, it)))
                     return rc;
                 if ((rc = stencil(z, r, 1, RED_NORM, nullptr, 1, true)))
                     return rc;
-                if ((rc = blas_step(B_CG_P, p, nullptr, z, nullptr, nullptr, nullptr, nullptr, 2, 1, -1, it)))
+                if ((rc = blas_step(B_CG_XP, p, x, z, nullptr, nullptr, nullptr, nullptr, 2, 1, -1, it)))
                     return rc;
                 if ((rc = mark(it, &stop)))
                     return rc;
@@ -769,13 +769,13 @@ struct Engine {
                     return rc;
                 if ((rc = fin(F_CG_ALPHA, 0, -1, -1, it, tol2)))
                     return rc;
-                if ((rc = blas(B_CG_XR, x, r, p, w, nullptr, nullptr, 0, true)))
+                if ((rc = blas(B_CG_R, nullptr, r, nullptr, w, nullptr, nullptr, 0, true)))
                     return rc;
                 if ((rc = stencil(z, r, 1, RED_NORM, nullptr, 1, true)))
                     return rc;
                 if ((rc = fin(F_CG_BETA, 0, 1, -1, it, tol2)))
                     return rc;
-                if ((rc = blas(B_CG_P, p, nullptr, z, nullptr, nullptr, nullptr, -1, true)))
+                if ((rc = blas(B_CG_XP, p, x, z, nullptr, nullptr, nullptr, -1, true)))
                     return rc;
                 if ((rc = mark(it, &stop)))
                     return rc;
@@ -869,21 +869,26 @@ struct Engine {
         return WL_OK;
     }
 
-    // out[r] = |b - D x|^2 per right-hand side, into host array (synchronous).
-    int true_res2(void *x, const void *b, double *out_host)
+    // v[0] = b - D x, with |r|^2 into partial set `slot` (negative: r alone).
+    int residual(const void *x, const void *b, int slot)
     {
         int rc;
         void *w = v[1], *r = v[0];
         if (lats.empty() && op->ns == 0 && (prec == WL_F64 || prec == WL_F32)) {
-            // one pass: r = b - D x with |r|^2 in the stencil's epilogue
-            if ((rc = stencil(r, x, 0, RED_NORM, b, 0, false, nullptr, nullptr, 3)))
-                return rc;
-        } else {
-            if ((rc = stencil(w, x, 0, RED_NONE, nullptr, -1)))
-                return rc;
-            if ((rc = blas(B_RES, r, nullptr, b, w, nullptr, nullptr, 0)))
-                return rc;
+            // one pass: r = b - D x (with |r|^2) in the stencil's epilogue
+            return stencil(r, x, 0, slot >= 0 ? RED_NORM : RED_NONE, b, slot, false, nullptr, nullptr, 3);
         }
+        if ((rc = stencil(w, x, 0, RED_NONE, nullptr, -1)))
+            return rc;
+        return blas(B_RES, r, nullptr, b, w, nullptr, nullptr, slot >= 0 ? slot : 0);
+    }
+
+    // out[r] = |b - D x|^2 per right-hand side, into host array (synchronous).
+    int true_res2(void *x, const void *b, double *out_host)
+    {
+        int rc;
+        if ((rc = residual(x, b, 0)))
+            return rc;
         if ((rc = fin(F_SUM, 0, -1, -1, 0, 0.0, hb->dev(out_host))))
             return rc;
         WL_TRY(hipStreamSynchronize(st));
@@ -1139,9 +1144,7 @@ int solve_mixed(int solver, const wl_op *hi, const wl_op *lo, void *x, const voi
             WL_TRY(accum());
             if ((e = L.blas(B_ZERO, e_lo, nullptr, nullptr, nullptr, nullptr, nullptr, -1)))
                 return e;
-            if ((e = H.stencil(H.v[1], x, 0, RED_NONE, nullptr, -1)))
-                return e;
-            if ((e = H.blas(B_RES, H.v[0], nullptr, b, H.v[1], nullptr, nullptr, 0)))
+            if ((e = H.residual(x, b, -1)))
                 return e;
             WL_TRY(convert(H.v[0], L.v[0]));
             if (solver == WL_SOLVER_BICGSTAB) {
