@@ -220,7 +220,9 @@ typedef struct {
                              reductions, not the stencil, bound the solver):
                              0 = merged two-phase iterations (CGNR: 4 kernels and 2
                              finalizes per iteration; BiCGStab: 4 kernels and 3
-                             finalizes, see below);
+                             finalizes, see below; with one right-hand side on up
+                             to 16384 sites (even-odd: even sites) the updates do
+                             the scalar steps themselves: 4 kernels, no finalize);
                              1 = one reduction phase per iteration.  CGNR in
                              Chronopoulos and Gear's form: z = D^dag r and q = D z
                              with their norms, one finalize (alpha from
@@ -244,7 +246,7 @@ typedef struct {
     double true_rel_res;  /* final true relative residual ||b - D x|| / ||b|| (FP64) */
     double seconds;       /* wall time of the whole call */
     int kernels;          /* kernel launches of the call (finalizes included) */
-    int finalizes;        /* single-workgroup finalize launches (the reduction phases) */
+    int finalizes;        /* finalize launches (the reduction phases that an update does not close itself) */
 } wl_solve_stats;
 
 /* Device workspace needed by a solve (hi op; lo op or NULL; solver id). */
