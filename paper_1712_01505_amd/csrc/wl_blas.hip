@@ -12,6 +12,7 @@
 //
 // Inner product <a, b> = sum conj(a_i) b_i; norms and dots accumulate in FP64.
 #include <algorithm>
+#include <type_traits>
 
 #include "wl_internal.h"
 
@@ -524,16 +525,34 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
     } else {
         sc = p.sc[col];
     }
-    // operand k of the op, at f
-    auto operand = [&](int k, const void *f, uint32_t s, cx<T>(&v)[12]) {
+    // Operand k of the op, at f: preloaded where FUSE, else loaded here.
+    //
+    // `last`: nothing reads these values again before they are overwritten or
+    // a whole iteration has passed (x; t, v and s after the update of r and p;
+    // the residual that s replaces; w and z of CGNR), so they go past the
+    // caches, and so does x when it is stored.  What the next kernel reads --
+    // r, p, s and v in front of their dots -- is then still in the 256 MB
+    // Infinity Cache when that kernel starts.  The gain is where an iteration's
+    // live vectors are near the cache's size: CGNR on the 5-d operator
+    // (16^3x32, Ns = 8, F32, 96 MB a vector) 187 -> 153 ms for the solve,
+    // BiCGStab on FP16 32^3x64 (109 MB a vector) 73.1 -> 70.9 ms and its
+    // even-odd form 35.6 -> 35.0, F32 24^3x48 51.4 -> 49.5, F16 24^3x48
+    // 24.1 -> 22.7; unchanged where everything fits (16^3x32).  Links and the
+    // stencil's own operands are left cached: with links past the caches as
+    // well 24^3x48 F32 gains another 10 % but FP16 24^3x48 and the 16^3x32
+    // solves lose 3 to 5 %, and a group of right-hand sides, which reads a
+    // link several times, loses 20 %.
+    auto fetch = [&](auto last, int k, const void *f, uint32_t s, cx<T>(&v)[12]) {
         if constexpr (FUSE) {
 #pragma unroll
             for (int i = 0; i < 12; ++i)
                 v[i] = pre[k][i];
         } else {
-            load_site<P>(f, V, nr, s, r, v);
+            load_site<P, decltype(last)::value>(f, V, nr, s, r, v);
         }
     };
+    auto operand = [&](int k, const void *f, uint32_t s, cx<T>(&v)[12]) { fetch(std::false_type{}, k, f, s, v); };
+    auto operand_last = [&](int k, const void *f, uint32_t s, cx<T>(&v)[12]) { fetch(std::true_type{}, k, f, s, v); };
     if (p.skip_frozen && (OP == B_CG_XP ? sc.frozen == 1 : sc.frozen != 0))  // whole workgroup
         return;
     if (OP == B_CG_RESTART && !sc.restart)
@@ -556,7 +575,7 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             const T a = (T)sc.alpha.x;
             cx<T> rr[12], w[12];
             operand(0, Y1, s, rr);
-            operand(1, A1, s, w);
+            operand_last(1, A1, s, w);
 #pragma unroll
             for (int k = 0; k < 12; ++k)
                 rr[k] = rfma(-a, w[k], rr[k]);
@@ -570,14 +589,14 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             const T a = (T)sc.alpha.x, b = (T)sc.beta.x;
             cx<T> x[12], pp[12], z[12];
             operand(0, Y0, s, pp);
-            operand(1, A0, s, z);
-            operand(2, Y1, s, x);
+            operand_last(1, A0, s, z);
+            operand_last(2, Y1, s, x);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 x[k] = rfma(a, pp[k], x[k]);
                 pp[k] = rfma(b, pp[k], z[k]);
             }
-            store_site<P>(Y1, V, nr, s, r, x);
+            store_site<P, true>(Y1, V, nr, s, r, x);
             store_site<P>(Y0, V, nr, s, r, pp);
         } else if constexpr (OP == B_BI_P) {  // p = r + beta (p - omega v)
             const cx<T> b{(T)sc.beta.x, (T)sc.beta.y}, om{(T)sc.omega.x, (T)sc.omega.y};
@@ -594,7 +613,7 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
         } else if constexpr (OP == B_BI_S) {  // s = r - alpha v (|s|^2 comes with t = D s)
             const cx<T> a{(T)sc.alpha.x, (T)sc.alpha.y};
             cx<T> rr[12], v[12];
-            operand(0, A0, s, rr);
+            operand_last(0, A0, s, rr);
             operand(1, A1, s, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k)
@@ -707,10 +726,10 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
             const cx<T> a{(T)sc.alpha.x, (T)sc.alpha.y}, om{(T)sc.omega.x, (T)sc.omega.y};
             const cx<T> b{(T)sc.beta.x, (T)sc.beta.y};
             cx<T> x[12], pp[12], ss[12], t[12];
-            operand(0, Y0, s, x);
+            operand_last(0, Y0, s, x);
             operand(1, Y2, s, pp);
-            operand(2, A1, s, ss);
-            operand(3, A2, s, t);
+            operand_last(2, A1, s, ss);
+            operand_last(3, A2, s, t);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 x[k] = cfma(a, pp[k], x[k]);
@@ -718,11 +737,11 @@ __global__ __launch_bounds__(256) void blas_kernel(BlasParams p)
                 ss[k] = cfma(cx<T>{-om.re, -om.im}, t[k], ss[k]);
             }
             round_if_scaled<P>(ss);
-            store_site<P>(Y0, V, nr, s, r, x);
+            store_site<P, true>(Y0, V, nr, s, r, x);
             store_site<P>(Y1, V, nr, s, r, ss);
             red[0] += n2(ss);
             cx<T> v[12];
-            operand(4, A3, s, v);
+            operand_last(4, A3, s, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 const cx<T> d = cfma(cx<T>{-om.re, -om.im}, v[k], pp[k]);

@@ -184,7 +184,36 @@ __device__ __forceinline__ const float *scale_ptr(const void *base, uint32_t V, 
     return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + (size_t)nrhs * V * 48);
 }
 
-template <int P>
+// One 16-byte chunk; NT: past the caches, for a value that nothing reads soon.
+template <bool NT>
+__device__ __forceinline__ double2 ld16(const double2 *p)
+{
+    if constexpr (NT) {
+        const nt_d2 d = __builtin_nontemporal_load(reinterpret_cast<const nt_d2 *>(p));
+        return make_double2(d.x, d.y);
+    } else
+        return *p;
+}
+template <bool NT>
+__device__ __forceinline__ float4 ld16(const float4 *p)
+{
+    if constexpr (NT) {
+        const nt_f4 d = __builtin_nontemporal_load(reinterpret_cast<const nt_f4 *>(p));
+        return make_float4(d.x, d.y, d.z, d.w);
+    } else
+        return *p;
+}
+template <bool NT>
+__device__ __forceinline__ uint4 ld16(const uint4 *p)
+{
+    if constexpr (NT) {
+        const nt_u4 d = __builtin_nontemporal_load(reinterpret_cast<const nt_u4 *>(p));
+        return make_uint4(d.x, d.y, d.z, d.w);
+    } else
+        return *p;
+}
+
+template <int P, bool NT = false>
 __device__ __forceinline__ void load_site(const void *base, uint32_t V, int nrhs, uint32_t s, int rhs,
                                           cx<typename Traits<P>::real> (&v)[12])
 {
@@ -193,14 +222,14 @@ __device__ __forceinline__ void load_site(const void *base, uint32_t V, int nrhs
         const double2 *b = reinterpret_cast<const double2 *>(base) + off;
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-            double2 d = b[(size_t)k * V];
+            double2 d = ld16<NT>(b + (size_t)k * V);
             v[k] = cx<double>{d.x, d.y};
         }
     } else if constexpr (P == F32) {
         const float4 *b = reinterpret_cast<const float4 *>(base) + off;
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            float4 d = b[(size_t)k * V];
+            float4 d = ld16<NT>(b + (size_t)k * V);
             v[2 * k] = cx<float>{d.x, d.y};
             v[2 * k + 1] = cx<float>{d.z, d.w};
         }
@@ -209,7 +238,7 @@ __device__ __forceinline__ void load_site(const void *base, uint32_t V, int nrhs
         const float sc = scale_ptr<P>(base, V, nrhs)[(size_t)rhs * V + s];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            uint4 d = b[(size_t)k * V];
+            uint4 d = ld16<NT>(b + (size_t)k * V);
             cx<float> a0 = unpack2<P>(d.x), a1 = unpack2<P>(d.y), a2 = unpack2<P>(d.z), a3 = unpack2<P>(d.w);
             v[4 * k + 0] = cx<float>{a0.re * sc, a0.im * sc};
             v[4 * k + 1] = cx<float>{a1.re * sc, a1.im * sc};
