@@ -114,17 +114,36 @@ __device__ __forceinline__ const char *slice_scales(const void *f, uint32_t V, i
 }
 
 template <int P>
-__device__ __forceinline__ void raw_spinor(const StencilParams &p, uint32_t xyz, uint32_t toff, int rhs, RawSp<P> &r)
+__device__ __forceinline__ void raw_field(const void *f, const StencilParams &p, uint32_t xyz, uint32_t toff, int rhs, RawSp<P> &r)
 {
     using C = typename RawSp<P>::C;
-    const char *b = slice_chunks<P>(p.in, p.V, rhs, toff);
+    const char *b = slice_chunks<P>(f, p.V, rhs, toff);
 #pragma unroll
     for (int k = 0; k < Traits<P>::NCH; ++k)
         r.sp[k] = at<C>(b + (size_t)k * p.V * 16, xyz * 16u);
     if constexpr (Traits<P>::SCALED)
-        r.sc = at<float>(slice_scales<P>(p.in, p.V, p.nrhs, rhs, toff), xyz * 4u);
+        r.sc = at<float>(slice_scales<P>(f, p.V, p.nrhs, rhs, toff), xyz * 4u);
     else
         r.sc = 1.f;
+}
+template <int P>
+__device__ __forceinline__ void raw_spinor(const StencilParams &p, uint32_t xyz, uint32_t toff, int rhs, RawSp<P> &r)
+{
+    raw_field<P>(p.in, p, xyz, toff, rhs, r);
+}
+// The values of a raw 16-bit site, as load_site
+template <int P>
+__device__ __forceinline__ void raw_values(const RawSp<P> &r, cx<float> (&v)[12])
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint4 d = r.sp[k];
+        const cx<float> a0 = unpack2<P>(d.x), a1 = unpack2<P>(d.y), a2 = unpack2<P>(d.z), a3 = unpack2<P>(d.w);
+        v[4 * k + 0] = cx<float>{a0.re * r.sc, a0.im * r.sc};
+        v[4 * k + 1] = cx<float>{a1.re * r.sc, a1.im * r.sc};
+        v[4 * k + 2] = cx<float>{a2.re * r.sc, a2.im * r.sc};
+        v[4 * k + 3] = cx<float>{a3.re * r.sc, a3.im * r.sc};
+    }
 }
 
 template <int P>
@@ -207,8 +226,13 @@ __device__ __forceinline__ uint32_t halo_site(const StencilParams &p, const Bric
 }
 
 // Wavefronts per SIMD asked of the compiler: three in 16 bits where the fused
-// reduction leaves the registers for it (168 each).
-constexpr int brick_waves(int prec, int red) { return prec >= BF16S && red != RED_BICG && red != RED_SR ? 3 : 1; }
+// reduction leaves the registers for it (168 each; BF16 <r, D p>, which decodes
+// its links with more instructions, 134 us at 32^3 x 64 without the bound and
+// 148 with it; FP16 131 and 129).
+constexpr int brick_waves(int prec, int red)
+{
+    return prec < BF16S || red == RED_BICG || red == RED_SR || (prec == BF16S && red == RED_DOTV) ? 1 : 3;
+}
 
 template <int P, int DAG, int RED, int APPLY, int MULTI>
 __global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(StencilParams p, BrickGeom g)
@@ -219,6 +243,16 @@ __global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(Stencil
     constexpr int NV = red_nval(RED);
     constexpr int SF = DAG ? 1 : -1;  // forward hops use (1 + SF g), backward (1 - SF g)
     constexpr bool LINKS_EARLY = Traits<P>::SCALED;  // FP32 and FP64 load each hop's link where it is used (registers)
+    // The reduction's own vector (aux).  A load issued after the stores of the
+    // result waits for them as well (one counter, in order), so it is issued
+    // before them: in 16 bits with the other loads of the step (13 registers),
+    // in FP32 and FP64 right in front of the stores.  32^3 x 64, us with the
+    // finalize, before and after: FP16 <r, D p> 134 and 129, BiCGStab's eight
+    // values 140 and 134; BF16 144 and 135, 157 and 151; FP32 204 and 202; FP64
+    // eight values 434 and 420.  FP64 <r, D p> stays behind the stores (411, in
+    // front 418).
+    constexpr bool AUX_EARLY = Traits<P>::SCALED && (RED == RED_DOTV || RED == RED_BICG);
+    constexpr bool AUX_AFTER = P == F64 && RED == RED_DOTV;
     extern __shared__ __align__(16) char smem_all[];
     __shared__ double lds_red[(NV > 0 ? NV : 1) * 4];
     int grp;
@@ -352,6 +386,9 @@ __global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(Stencil
             raw_spinor<P>(p, xo, g.nxyz * (uint32_t)(wf ? 0 : t + 1), rhs, nxt);
             RawHop<P> rf;
             raw_link<P>(p, xo, toff, 3, rf);
+            RawSp<P> ax;
+            if constexpr (AUX_EARLY)
+                raw_field<P>(p.aux, p, xo, toff, rhs, ax);
             RawHop<P> lnk[6];
             if constexpr (LINKS_EARLY) {
 #pragma unroll
@@ -431,6 +468,9 @@ __global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(Stencil
             }
             if constexpr (APPLY == 3)
                 residual_epilogue<P>(p, s, rhs, o);
+            cx<R_> v[12];
+            if constexpr ((RED == RED_DOTV || RED == RED_BICG) && !AUX_EARLY && !AUX_AFTER)
+                load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
             store_slice_q<P>(p, xo, toff, rhs, o);
             if constexpr (RED == RED_NORM || RED == RED_DOTIN_NORM) {
 #pragma unroll
@@ -445,8 +485,10 @@ __global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(Stencil
                 }
             }
             if constexpr (RED == RED_DOTV) {
-                cx<R_> v[12];
-                load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
+                if constexpr (AUX_EARLY)
+                    raw_values<P>(ax, v);
+                else if constexpr (AUX_AFTER)
+                    load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
 #pragma unroll
                 for (int i = 0; i < 12; ++i) {
                     red[0] = fma((double)v[i].re, (double)o[i].re, fma((double)v[i].im, (double)o[i].im, red[0]));
@@ -454,8 +496,8 @@ __global__ __launch_bounds__(256, brick_waves(P, RED)) void brick_kernel(Stencil
                 }
             }
             if constexpr (RED == RED_BICG) {
-                cx<R_> v[12];
-                load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
+                if constexpr (AUX_EARLY)
+                    raw_values<P>(ax, v);
                 bicg_values(self, o, v, red);
             }
             if constexpr (RED == RED_SR) {

@@ -171,6 +171,9 @@ __global__ __launch_bounds__(256) void twalk_kernel(StencilParams p, int T, uint
             }
             if constexpr (APPLY == 3)
                 residual_epilogue<P>(p, s, rhs, o);
+            cx<R_> v[12];  // ahead of the stores (see stencil_kernel)
+            if constexpr (RED == RED_DOTV || RED == RED_BICG)
+                load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
             store_site_q<P, true>(p.out, p.V, p.nrhs, s, rhs, o);
             if constexpr (RED == RED_NORM || RED == RED_DOTIN_NORM) {
 #pragma unroll
@@ -185,8 +188,6 @@ __global__ __launch_bounds__(256) void twalk_kernel(StencilParams p, int T, uint
                 }
             }
             if constexpr (RED == RED_DOTV) {
-                cx<R_> v[12];
-                load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
 #pragma unroll
                 for (int i = 0; i < 12; ++i) {
                     red[0] = fma((double)v[i].re, (double)o[i].re, fma((double)v[i].im, (double)o[i].im, red[0]));
@@ -194,8 +195,6 @@ __global__ __launch_bounds__(256) void twalk_kernel(StencilParams p, int T, uint
                 }
             }
             if constexpr (RED == RED_BICG) {
-                cx<R_> v[12];
-                load_site<P>(p.aux, p.V, p.nrhs, s, rhs, v);
                 bicg_values(self, o, v, red);  // accumulates over the t-walk
             }
             if constexpr (RED == RED_SR) {
@@ -268,10 +267,17 @@ __global__ __launch_bounds__(512) void stencil_kernel(StencilParams p)
         const T kap = (T)p.kappa;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            cx<T> o[12];
-            if constexpr (APPLY || RED == RED_DOTIN_NORM) {
-                cx<T> in[12];
+            // every operand of the epilogue and of the reduction ahead of the
+            // stores, which a later load would wait for too; the reduction's
+            // input values are the epilogue's (16^3 x 32, us with the finalize:
+            // FP32 <r, D p> 16.9 and 16.3, eight values 18.1 and 17.3; 24^3 x 48
+            // FP32 eight values 69 and 64)
+            cx<T> o[12], in[12], v[12];
+            if constexpr (RED == RED_BICG || RED == RED_DOTV)
+                load_site<P>(p.aux, p.V, p.nrhs, s, r0 + r, v);
+            if constexpr (APPLY || RED == RED_DOTIN_NORM || RED == RED_BICG || RED == RED_SR)
                 load_site<P>(p.in, p.V, p.nrhs, s, r0 + r, in);
+            if constexpr (APPLY || RED == RED_DOTIN_NORM) {
                 if constexpr (APPLY == 2) {
                     dw_epilogue<P, DAG>(p, s, r0 + r, in, acc[r], o);
                 } else if constexpr (APPLY) {
@@ -311,22 +317,16 @@ __global__ __launch_bounds__(512) void stencil_kernel(StencilParams p)
                 red[NV * r + NV - 1] = n2;
             }
             if constexpr (RED == RED_BICG) {
-                cx<T> in[12], v[12];
-                load_site<P>(p.in, p.V, p.nrhs, s, r0 + r, in);
-                load_site<P>(p.aux, p.V, p.nrhs, s, r0 + r, v);
                 bicg_values(in, o, v, &red[NV * r]);
             }
             if constexpr (RED == RED_SR) {
-                cx<T> in[12], a[12], b[12], c[12];
-                load_site<P>(p.in, p.V, p.nrhs, s, r0 + r, in);
+                cx<T> a[12], b[12], c[12];
                 load_site<P>(p.aux, p.V, p.nrhs, s, r0 + r, a);
                 load_site<P>(p.aux2, p.V, p.nrhs, s, r0 + r, b);
                 load_site<P>(p.aux3, p.V, p.nrhs, s, r0 + r, c);
                 sr_values(in, o, a, b, c, &red[NV * r]);
             }
             if constexpr (RED == RED_DOTV) {
-                cx<T> v[12];
-                load_site<P>(p.aux, p.V, p.nrhs, s, r0 + r, v);
                 double re = 0.0, im = 0.0;
 #pragma unroll
                 for (int k = 0; k < 12; ++k) {
