@@ -83,3 +83,19 @@ def test_cgnr_columns_that_stop_apart(W, dims, precision):
         xr, sr = W.solve(U, b[r], KAPPA, x0=x0[r], **kw)
         assert sr["converged"] and abs(sr["iters"] - s[r]["iters"]) <= 1
         assert float((x[r] - xr).norm()) <= 100 * tol * float(xr.norm())
+
+
+def test_runs_on_the_current_stream(W):
+    """The default stream and a side stream: the handle passed is torch's, and a solve gives the
+    same bits on either."""
+    U, b = _system((8, 8, 4, 4), 5)
+    ref = W.solve(U, b[0], KAPPA, precision="f64", tol=1e-10)
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side):
+        stream.wait_stream(torch.cuda.default_stream())
+        with torch.cuda.stream(stream):
+            assert W._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
+            x = W.solve(U, b[0], KAPPA, precision="f64", tol=1e-10)
+        stream.synchronize()
+        assert torch.equal(x, ref)
+    assert side.cuda_stream != torch.cuda.default_stream().cuda_stream
