@@ -271,7 +271,8 @@ static bool launch_ok(const wl_op *op, int nrhs, const LaunchCfg &c);
 // chip walks its units in rounds of 256 k workgroups, each of T + 1 slices
 // (the walk's start costs about one), and a slice costs its sites' own bytes
 // plus its halo's, which come from L2 (half weight; the x faces are single
-// sites of other rows, six times that).  The fastest measured shape at 32^3 x 64
+// sites of other rows, six times that).  Walks of up to 64 slices: two columns
+// of FP64 at 32^3 x 64 take 623 us with 64, 650 with 32.  The fastest measured shape at 32^3 x 64
 // is the estimate's in FP64 and FP32 (32 x 2 x 4, walks of 32 and 16) and
 // within 1 % of it for the 16-bit apply; with a reduction 16 bits run best in
 // bricks of one wavefront (FP16, the eight BiCGStab values: 126 us, 256
@@ -302,7 +303,7 @@ static bool brick_default(const wl_op *op, int nrhs, int red, LaunchCfg &best)
                 const double idle = prec == WL_F64 && nb == 192 ? 1.15 : 1.0;  // a SIMD without a wavefront
                 const double slice = (nb * site + 0.5 * sp * (6.0 * fx + fy + fz)) * idle;
                 const double units = (double)(L[0] / bx) * (L[1] / by) * (L[2] / bz) * nrhs;
-                for (int T = 2; T <= 32 && T <= L[3]; ++T) {
+                for (int T = 2; T <= 64 && T <= L[3]; ++T) {
                     if (L[3] % T != 0)
                         continue;
                     const double cost = std::ceil(units * (L[3] / T) / (256.0 * k)) * k * (T + 1) * slice;
@@ -372,7 +373,16 @@ static LaunchCfg default_launch(const wl_op *op, int nrhs, int red)
         // below the line, 32 x 16 x 24 x 40 x 8, FP32: 321 and 300)
         if (L[0] % 32 == 0 && 3.0 * spinor_site_bytes(prec) * L[0] * L[1] * L[2] * nrhs > 32.0 * (1 << 20) &&
             brick_default(op, nrhs, RED_NONE, c)) {
-            c.xcd = 0;
+            // One contiguous range of bricks per XCD, where the halos of
+            // neighbours meet in its L2, in FP64 (32^3 x 64 x 8: 2550 us, plain
+            // order 2695; 32^2 x 16^2 x 12: 477 and 502) and for FP32's long walks
+            // (32^3 x 64 x 8: 1125 and 1160; 64 x 16^2 x 32 x 8: 333 and 350; but
+            // walks of 16, 32^4 x 6: 461 and 452), with eight bricks of a t-slice
+            // or more per XCD (six, 32 x 16 x 24 x 64 x 8 in FP64: 996 and 980).
+            // 16 bits, whose slices pass faster than the links they share, in
+            // plain order (FP16: 801, 774)
+            const long bricks = (long)(L[0] / c.bx) * (L[1] / c.by) * (L[2] / c.bz);
+            c.xcd = bricks >= 64 && (prec == WL_F64 || (prec == WL_F32 && c.tsteps >= 24)) ? 1 : 0;
             return c;
         }
         c.lanes = nrhs % 2 == 0 ? 2 : 1;
