@@ -177,7 +177,7 @@ int wilson_schur_apply(const wl_op *op, void *out_e, const void *in_e, void *tmp
  * wl_set_launch (nrhs = 5-d vectors; one slice per thread, variants 0..2
  * and the t-walks 4..6, slices across lanes allowed; the library itself may
  * run large lattices in brick walks, one slice each, which wl_get_launch
- * then reports as variant 7) and wl_op_destroy; the Wilson entry points, solve_bicgstab (its spectrum
+ * then reports as variant 7 and wl_set_launch takes back) and wl_op_destroy; the Wilson entry points, solve_bicgstab (its spectrum
  * reaches Re < 0), the force and multi-lattice plans reject it with
  * WL_EINVAL. */
 int wl_dw_op_create(const wl_geom *g, double m0, double m, int Ns, int prec, const void *U_packed, wl_op **out);

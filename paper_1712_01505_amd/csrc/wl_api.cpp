@@ -1281,6 +1281,27 @@ int wl_get_launch(const wl_op *op, int nrhs, wl_launch *cfg)
     return WL_OK;
 }
 
+// Whether c is a shape that the library has for nrhs columns: the one in use,
+// the untuned one or a tuned one.
+static bool chosen_here(const wl_op *op, int nrhs, const LaunchCfg &c)
+{
+    const auto same = [&](const LaunchCfg &o) {
+        return c.block == o.block && c.rpt == o.rpt && c.xcd == o.xcd && c.var == o.var && c.lanes == o.lanes &&
+               c.bx == o.bx && c.by == o.by && c.bz == o.bz && c.tsteps == o.tsteps && c.wpe == o.wpe &&
+               c.gmaj == o.gmaj;
+    };
+    for (int red = RED_NONE; red <= RED_LAST; ++red)
+        for (int d = 0; d <= 1; ++d) {
+            if (same(launch_for(op, nrhs, red, d)) || same(default_launch(op, nrhs, red)))
+                return true;
+            std::lock_guard<std::mutex> lk(g_tune_mu);
+            auto it = g_tune.find(tune_key(op, nrhs, d, red));
+            if (it != g_tune.end() && same(it->second.c))
+                return true;
+        }
+    return false;
+}
+
 int wl_set_launch(wl_op *op, int nrhs, const wl_launch *cfg)
 {
     if (!op || nrhs < 1 || !cfg)
@@ -1302,8 +1323,9 @@ int wl_set_launch(wl_op *op, int nrhs, const wl_launch *cfg)
         return WL_EINVAL;
     }
     c.gmaj = cfg->rhs_major;
-    // a domain-wall brick walk is the library's own choice only
-    if (!launch_ok(op, nrhs, c) || (op->ns > 0 && c.var == VAR_BRICK))
+    // a domain-wall brick walk is the library's own choice: taken back from a
+    // caller who got it from wl_get_launch, otherwise refused
+    if (!launch_ok(op, nrhs, c) || (op->ns > 0 && c.var == VAR_BRICK && !chosen_here(op, nrhs, c)))
         return WL_EINVAL;
     std::lock_guard<std::mutex> lk(op->mu);
     for (int red = RED_NONE; red <= RED_LAST; ++red)  // every stencil of this nrhs

@@ -31,9 +31,16 @@ def test_default_shape_is_valid_everywhere():
         h = _op(dims, prec, ns)
         c = wilson.wl_launch()
         assert wilson.lib().wl_get_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK
-        # a domain-wall brick walk is the library's own choice: not offered to callers
-        want = wilson.WL_EINVAL if ns and c.variant == wilson.VAR_BRICK else wilson.WL_OK
-        assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(c)) == want, (dims, prec, ns, nrhs, c.variant)
+        assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK, (dims, prec, ns, nrhs, c.variant)
+        if ns and c.variant == wilson.VAR_BRICK:  # the library's own choice: taken back, no other is taken
+            o = wilson.wl_launch()
+            ctypes.memmove(ctypes.byref(o), ctypes.byref(c), ctypes.sizeof(c))
+            c.block, c.variant, c.t_steps, c.xcd_remap, c.rhs_lanes, c.brick[:] = 64, 0, 0, 0, 1, [0, 0, 0]
+            assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(c)) == wilson.WL_OK
+            assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(o)) == wilson.WL_OK
+            o.xcd_remap = 1 - o.xcd_remap
+            assert wilson.lib().wl_set_launch(h, nrhs, ctypes.byref(o)) == wilson.WL_EINVAL
+            c.variant = wilson.VAR_BRICK
         seen.add((prec, c.variant, ns > 0, nrhs > 1))
         wilson.lib().wl_op_destroy(h)
     for prec in (wilson.WL_F64, wilson.WL_F32, wilson.WL_F16S):
