@@ -442,7 +442,17 @@ static LaunchCfg default_launch(const wl_op *op, int nrhs, int red)
     }
     c.lanes = prec >= WL_BF16S && nrhs % 2 == 0 ? 2 : 1;
     c.block = c.lanes == 2 ? 128 : 256;
-    c.var = prec == WL_F64 ? 1 : 2;
+    // loads two hops ahead, or one where the registers of two leave fewer
+    // wavefronts than the reuse between columns wants: an odd number of 16-bit
+    // columns, in BF16 (24^3 x 32, three: 53.5 and 56.4; 20^3 x 40, five: 67.0
+    // and 69.8; with a reduction up to 2^21 sites of all columns, 22 x 18 x 14 x
+    // 27, five, <r, D p>: 41.4 and 43.7, but 20^3 x 40, nine: 161 and 157) and
+    // for FP16's eight BiCGStab values (20^3 x 40, five: 86.5 and 92.5; <r, D p>
+    // 80 and 77.5, apply equal)
+    const bool one_ahead = c.lanes == 1 && (prec == WL_BF16S  ? red == RED_NONE || VN < (1u << 21)
+                                            : prec == WL_F16S ? red == RED_BICG || red == RED_SR
+                                                              : prec == WL_F64);
+    c.var = one_ahead ? 1 : 2;
     c.xcd = order(c.block / c.lanes);
     return c;
 }
@@ -531,8 +541,9 @@ LaunchCfg launch_for(const wl_op *op, int nrhs, int red, int dagger)
     for (int k = 0; k < 4 && !have; ++k) {
         {
             std::lock_guard<std::mutex> lk(o->mu);
+            // (an untuned shape of another reduction stands for no choice)
             auto it = o->launch.find(launch_key(nrhs, order[k][0], order[k][1]));
-            if (it != o->launch.end()) {
+            if (it != o->launch.end() && !it->second.untuned) {
                 c = it->second;
                 have = true;
                 break;
@@ -546,6 +557,7 @@ LaunchCfg launch_for(const wl_op *op, int nrhs, int red, int dagger)
             have = true;
         }
     }
+    c.untuned = !have;
     std::lock_guard<std::mutex> lk(o->mu);
     o->launch[launch_key(nrhs, red, dagger)] = c;
     return c;

@@ -31,6 +31,8 @@ struct LaunchCfg {
     // several right-hand-side groups: 0 = the groups of a tile back to back
     // on one XCD, 1 = one group after the other over the whole lattice
     int gmaj = 0;
+    // kept for its own (columns, reduction, dagger) only: nobody chose it
+    bool untuned = false;
 };
 
 }  // namespace wl

@@ -116,3 +116,30 @@ def test_domain_wall_bricks(dims, ns, prec):
         x, st = wilson.dw_solve(U, psi, -1.8, 0.05, precision="f64", tol=1e-9, return_stats=True)
         r = psi - wilson.dw_apply(U, x, -1.8, 0.05, op=op)
         assert st["converged"] and float(r.norm() / psi.norm()) <= 1e-9
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,nrhs,prec", [((32, 32, 32, 20), 1, "bf16"), ((20, 20, 12, 8), 3, "f16"),
+                                            ((32, 32, 32, 24), 1, "f64")])
+def test_untuned_reduction_shape_does_not_depend_on_earlier_calls(dims, nrhs, prec):
+    """A fused reduction on an operator that has already been applied: the same bits as on a new
+    operator (each launch keeps its own untuned shape)."""
+    torch = pytest.importorskip("torch")
+    Lx, Ly, Lz, Lt = dims
+    U = torch.from_numpy(inputs.near_unity_gauge((2, 2, 2, 2), 0.3, seed=3)).to("cuda")
+    U = U.repeat(1, Lt // 2, Lz // 2, Ly // 2, Lx // 2, 1, 1)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    psi = torch.view_as_complex(torch.randn(nrhs, Lt, Lz, Ly, Lx, 4, 3, 2, dtype=torch.float64, device="cuda",
+                                            generator=g))
+    got = []
+    for first in (False, True):
+        op = wilson.Operator.create(U, 0.1255, wilson.PREC[prec])
+        src, out = op.pack(psi), op.new_field(nrhs)
+        v = op.pack(psi.roll(1, 1))
+        if first:
+            op.apply_packed(out, src, nrhs)
+        for kind in (wilson.WL_DOT_BICG, wilson.WL_DOT_V):
+            dots = wilson.apply_dot(op, out, src, v, nrhs=nrhs, kind=kind)
+            got.append((first, kind, out.clone(), dots))
+    for a, b in zip(got[:2], got[2:]):
+        assert torch.equal(a[2], b[2]) and torch.equal(a[3], b[3])
