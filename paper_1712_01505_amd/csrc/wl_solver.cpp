@@ -5,7 +5,8 @@
 //
 // Every vector operation is a kernel on the caller's stream; the scalar
 // recurrences live on the device (wl_blas.hip), so an iteration issues only
-// kernel launches; the finalize kernels mirror each column's status into
+// kernel launches; the finalize kernels (for one column of a small lattice the
+// updates themselves) mirror each column's status into
 // host-visible memory, and the host checks it behind a lookahead of
 // `check_every` queued iterations (HIP events, no copies, no stream drain
 // while iterating).  All right-hand sides run together; a converged
