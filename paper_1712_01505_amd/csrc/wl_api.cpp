@@ -274,16 +274,24 @@ static bool launch_ok(const wl_op *op, int nrhs, const LaunchCfg &c);
 // sites of other rows, six times that).  Walks of up to 64 slices: two columns
 // of FP64 at 32^3 x 64 take 623 us with 64, 650 with 32.  The fastest measured shape at 32^3 x 64
 // is the estimate's in FP64 and FP32 (32 x 2 x 4, walks of 32 and 16) and
-// within 1 % of it for the 16-bit apply; with a reduction 16 bits run best in
-// bricks of one wavefront (FP16, the eight BiCGStab values: 126 us, 256
-// sites 137), whose barriers wait for nobody.  False if no shape fits.
+// within 1 % of it for the 16-bit apply.  With a reduction 16 bits run best in
+// bricks of one wavefront, whose barriers wait for nobody (FP16, the eight
+// BiCGStab values, with the finalize: 48^3 x 64 456 us, 128 to 256 sites 508;
+// 32 x 24 x 48 x 50 126 and 141); FP16 <r, D p> and |D p|^2 in the apply's
+// (32^3 x 64: 120 us, one wavefront 128.5, and 102 and 109; 32 x 24 x 48 x 50:
+// 106 and 119), but without rows of 32 sites not always (48 x 24^2 x 64: 115
+// and 109).  False if no shape fits.
 static bool brick_default(const wl_op *op, int nrhs, int red, LaunchCfg &best)
 {
     const int *L = op->g.dims, prec = op->prec;
     const double site = 2.0 * spinor_site_bytes(prec) + 4.0 * link_site_bytes(prec), sp = spinor_site_bytes(prec);
     const bool half = prec >= WL_BF16S;
-    const int nb_lo = half && red != RED_NONE ? 64 : 128, nb_hi = half && red != RED_NONE ? 64 : 256;
-    const int waves_cu = prec == WL_F64 ? 4 : half && red == RED_NONE ? 12 : 8;
+    // 16-bit reductions in bricks of one wavefront, except FP16's with at most
+    // three values, which run three wavefronts per SIMD, on rows of 32 sites
+    const bool wide = prec == WL_F16S && red != RED_BICG && red != RED_SR && L[0] % 32 == 0;
+    const bool narrow = half && red != RED_NONE && !wide;
+    const int nb_lo = narrow ? 64 : 128, nb_hi = narrow ? 64 : 256;
+    const int waves_cu = prec == WL_F64 ? 4 : half && !narrow ? 12 : 8;
     double least = INFINITY;
     for (int bx = 32; bx >= 4; --bx) {
         if (L[0] % bx != 0)
